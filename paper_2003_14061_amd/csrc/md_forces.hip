@@ -170,18 +170,94 @@ __global__ void k_zero_forces(B b)
     }
 }
 
-// Six waves per SIMD (at most 80 VGPRs): three workgroups of the default
-// shape fit a CU by LDS, and the compiler's own allocation otherwise crosses
-// the five-wave line.
-template <typename F, typename Acc, int LANES, class B>
-__global__ __attribute__((amdgpu_waves_per_eu(6))) void k_forces_tiles(B b)
+// One home atom's sums, finished: its force written, its energy and half
+// virial added to e.
+template <typename F>
+__device__ __forceinline__ void home_finish(const KParams& p, const LeanOf<F>& a, int slot_i,
+                                            double (&e)[2])
 {
-    Wg wg;
-    KParams p;
-    if (!b.fetch(G_TILES, wg, p)) return;
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    __shared__ double red[(1024 / kWave) * 2];
-    const Tile g = tile_of(p, xcd_tile(wg.id, wg.n));
+    F fx, fy, fz;
+    double ui, wi;
+    lean_finish(p, a, fx, fy, fz, ui, wi);
+    static_cast<F*>(p.fx)[slot_i] = fx;
+    static_cast<F*>(p.fy)[slot_i] = fy;
+    static_cast<F*>(p.fz)[slot_i] = fz;
+    e[0] += ui;
+    e[1] += wi;
+    if (!isfinite(ui + (double)fx + (double)fy + (double)fz))
+        atomicOr(&p.dev->flags, (int)MD_FLAG_NONFINITE);
+}
+
+template <int LANES, typename T>
+__device__ __forceinline__ void lean_group_sum(Lean<T>& a)
+{
+    if (LANES > 1) {
+        a.fx = lane_group_sum<LANES>(a.fx);
+        a.fy = lane_group_sum<LANES>(a.fy);
+        a.fz = lane_group_sum<LANES>(a.fz);
+        a.q = lane_group_sum<LANES>(a.q);
+        a.s6 = lane_group_sum<LANES>(a.s6);
+    }
+}
+
+// A tile whose atoms fit in LDS, on a grid of at least 5 cells per side: from
+// the rows in registers (md_tiles.h).  A wave's home atoms are a contiguous
+// stretch; the length and the first chunk of each one's list are loaded
+// before the barrier that ends the staging, with which they overlap.  Bound
+// by VALU issue at dense states, by the chain of dependent loads at sparse
+// ones; against the tables (four barriers, a search per staged atom) it
+// measured 223 against 241 us at 2.048M LJ atoms, 16.5 against 19.2 us at
+// 256 000 WCA atoms and 56 against 65 us for 64 replicas (1.03M atoms).
+template <typename F, int LANES>
+__device__ __forceinline__ void forces_rows(const KParams& p, const Rows& t, char* smem,
+                                            double (&e)[2])
+{
+    MD_LDS double* p3 = (MD_LDS double*)smem;
+    constexpr int kPer = kWave / LANES;  // home atoms of a wave
+    const int lane = threadIdx.x & (kWave - 1);
+    const int w0 = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave) * kPer;
+    const int per_pass = (int)blockDim.x / LANES;
+    stage_rows<false>(p, t, p3, nullptr, nullptr, nullptr, nullptr);
+    bool staged = false;
+    for (int h0 = w0; h0 < t.nh || !staged; h0 += per_pass) {
+        const int h = h0 + lane / LANES;
+        int sub = lane % LANES;
+        asm volatile("" : "+v"(sub));  // the row offset below is formed anew in each pass
+        int slot_i = 0, eh = 0, cnt = 0;
+        uint64_t next = 0;
+        if (h0 < t.nh) {
+            int ds, de, row;
+            find_row<false>(t.hstart, t.d1 + t.e1 - t.hstart, t.e1 - t.hstart, h0, kPer, h, ds, de,
+                            row);
+            slot_i = atom_at(p, h < t.nh ? h + ds : 0);
+            eh = h + de;
+            if (h < t.nh) {
+                cnt = p.nl_count[slot_i];
+                if (sub <= p.cap / kChunk) next = p.nl64[(int64_t)sub * p.npad + slot_i];
+            }
+        }
+        if (!staged) __syncthreads();
+        staged = true;
+        if (h0 >= t.nh) break;
+        LeanOf<F> a;
+        if (h < t.nh) {
+            double xi, yi, zi;
+            lds_xyz(p3, eh, xi, yi, zi);
+            ForceOp<LeanOf<F>> op{p, a};
+            walk_staged<LANES>(p, p3, slot_i, sub, cnt, next, xi, yi, zi, op);
+        }
+        lean_group_sum<LANES>(a);
+        if (h < t.nh && sub == 0) home_finish<F>(p, a, slot_i, e);
+    }
+}
+
+// Any other tile (more than 64 staged rows, atoms past the LDS capacity, or a
+// grid of fewer than 5 cells per side, whose pairs take the minimum image by
+// rounding): through the cell tables in LDS.
+template <typename F, int LANES>
+__device__ __forceinline__ void forces_tables(const KParams& p, const Tile& g, char* smem,
+                                              double (&e)[2])
+{
     Stage s = stage_layout(p, smem);
     stage_tables(p, g, s);
     const int nh = home_count(s);
@@ -190,7 +266,6 @@ __global__ __attribute__((amdgpu_waves_per_eu(6))) void k_forces_tiles(B b)
     __syncthreads();
     const int per_pass = blockDim.x / LANES;
     const int sub = threadIdx.x % LANES;
-    double e[2] = {0.0, 0.0};
     for (int hb = 0; hb < nh; hb += per_pass) {
         const int h = hb + threadIdx.x / LANES;
         LeanOf<F> a;
@@ -209,26 +284,31 @@ __global__ __attribute__((amdgpu_waves_per_eu(6))) void k_forces_tiles(B b)
             asm volatile("" : "+v"(sub_p));
             walk_home<LANES>(p, s, mode, slot_i, sub_p, p.nl_count[slot_i], xi, yi, zi, op);
         }
-        if (LANES > 1) {
-            a.fx = lane_group_sum<LANES>(a.fx);
-            a.fy = lane_group_sum<LANES>(a.fy);
-            a.fz = lane_group_sum<LANES>(a.fz);
-            a.q = lane_group_sum<LANES>(a.q);
-            a.s6 = lane_group_sum<LANES>(a.s6);
-        }
-        if (h < nh && sub == 0) {
-            F fx, fy, fz;
-            double ui, wi;
-            lean_finish(p, a, fx, fy, fz, ui, wi);
-            static_cast<F*>(p.fx)[slot_i] = fx;
-            static_cast<F*>(p.fy)[slot_i] = fy;
-            static_cast<F*>(p.fz)[slot_i] = fz;
-            e[0] += ui;
-            e[1] += wi;
-            if (!isfinite(ui + (double)fx + (double)fy + (double)fz))
-                atomicOr(&p.dev->flags, (int)MD_FLAG_NONFINITE);
-        }
+        lean_group_sum<LANES>(a);
+        if (h < nh && sub == 0) home_finish<F>(p, a, slot_i, e);
     }
+}
+
+// Six waves per SIMD (at most 80 VGPRs): three workgroups of the default
+// shape fit a CU by LDS, and the compiler's own allocation otherwise crosses
+// the five-wave line.
+template <typename F, typename Acc, int LANES, class B>
+__global__ __attribute__((amdgpu_waves_per_eu(6))) void k_forces_tiles(B b)
+{
+    Wg wg;
+    KParams p;
+    if (!b.fetch(G_TILES, wg, p)) return;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    __shared__ double red[(1024 / kWave) * 2];
+    const Tile g = tile_of(p, xcd_tile(wg.id, wg.n));
+    double e[2] = {0.0, 0.0};
+    bool rows = rows_fit(p) && p.nc >= 5;
+    if (rows) {
+        const Rows t = row_table(p, g);
+        rows = t.total < p.scap;
+        if (rows) forces_rows<F, LANES>(p, t, smem, e);
+    }
+    if (!rows) forces_tables<F, LANES>(p, g, smem, e);
     block_sum<2>(e, red);
     if (threadIdx.x == 0) {
         p.fpart[2 * wg.id] = e[0];

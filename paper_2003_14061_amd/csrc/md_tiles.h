@@ -495,6 +495,31 @@ __device__ __forceinline__ void walk_list(const KParams& p, const Stage& s, int 
     }
 }
 
+// The same with every partner in LDS as its periodic image (p3), the first
+// chunk already in `next`.
+template <int LANES, class Op>
+__device__ __forceinline__ void walk_staged(const KParams& p, const MD_LDS double* p3, int slot_i,
+                                            int sub, int cnt, uint64_t next, double xi, double yi,
+                                            double zi, Op& op)
+{
+    const uint64_t* col = p.nl64 + slot_i;
+    const int nchunk = (cnt + kChunk - 1) / kChunk;
+    for (int c = sub; c < nchunk;) {
+        const uint64_t ch = next;
+        const int cn = c + LANES;
+        if (cn < nchunk) next = col[(int64_t)cn * p.npad];
+#pragma unroll
+        for (int k = 0; k < kChunk; ++k) {
+            const int e = (int)((uint32_t)(ch >> (16 * k)) & (uint32_t)kEntryMask);
+            double xj, yj, zj;
+            lds_xyz(p3, e, xj, yj, zj);
+            const double dx = xi - xj, dy = yi - yj, dz = zi - zj;
+            op(dx, dy, dz, dist2(dx, dy, dz), e, -1);
+        }
+        c = cn;
+    }
+}
+
 // The list of one home atom, with the image rule of its tile (mode, see
 // image_mode) and the LDS or global partner path.
 template <int LANES, class Op>
@@ -527,6 +552,172 @@ __device__ __forceinline__ void home_position(const KParams& p, const Stage& s, 
         xi = p.x[slot_i];
         yi = p.y[slot_i];
         zi = p.z[slot_i];
+    }
+}
+
+// ---- staged rows in registers ----
+//
+// The force pass needs of a tile's tables only where each staged row starts:
+// list entries are staged indices, and along a row the atoms' slots run on
+// from cell to cell (columns 0 .. kx+1), except that column 0 or kx+1 may sit
+// across the periodic boundary.  So each wave keeps the rows in registers, a
+// row per lane (at most 64 rows), read straight from cell_start: no table in
+// LDS, no workgroup scan, no barrier before the staging loads.  A 64-entry
+// stretch of staged entries (or of home atoms) finds its rows by one ballot
+// over the lanes' row starts and a scalar loop over the rows that begin inside
+// it (0.6 of them at the dense LJ state, 4.6 at the sparse WCA one), where a
+// search per entry took four to six dependent LDS reads.
+struct Rows {
+    int start;       // staged entry of the row's first atom (INT_MAX past the last row)
+    int d0, d1, d2;  // slot minus staged entry in column 0, columns 1 .. kx, column kx+1
+    int e1, e2;      // staged entries where columns 1 .. kx and column kx+1 begin
+    int hstart;      // home atoms before the row
+    int fl;          // wrap bits of the row: 2 / 4 y low / high, 8 / 16 z low / high
+    int total, nh;   // staged and home atoms of the tile (the same in every lane)
+    bool wl, wr;     // column 0 / column kx+1 wraps (the same in every lane)
+    bool wraps;      // some staged cell wraps (the same in every lane)
+};
+
+// The largest tile's rows fit a wave.
+__host__ __device__ __forceinline__ bool rows_fit(const KParams& p)
+{
+    return (p.ky_max + 2) * (p.kz_max + 2) <= kWave;
+}
+
+// The rows of tile g (every lane of the wave calls it).
+__device__ __forceinline__ Rows row_table(const KParams& p, const Tile& g)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int nc = p.nc, rows_y = g.ky + 2, nrows = rows_y * (g.kz + 2);
+    // lane / rows_y: exact for lane < 64, as 64 / 65536 < 1 / rows_y
+    const int inv = (65535 + rows_y) / rows_y;
+    const int c = (lane * inv) >> 16, b = lane - c * rows_y;
+    Rows t;
+    t.wl = g.cx0 == 0;
+    t.wr = g.cx0 + g.kx == nc;
+    t.wraps = t.wl || t.wr || g.cy0 == 0 || g.cy0 + g.ky == nc || g.cz0 == 0 || g.cz0 + g.kz == nc;
+    const int xl = t.wl ? nc - 1 : g.cx0 - 1, xr = t.wr ? 0 : g.cx0 + g.kx;
+    int a0 = 0, a1 = 0, a2 = 0, a3 = 0, l1 = 0, r0 = 0;
+    t.fl = 0;
+    bool home = false;
+    if (lane < nrows) {
+        const int yy = g.cy0 - 1 + b, zz = g.cz0 - 1 + c;
+        t.fl = (yy < 0 ? 2 : 0) | (yy >= nc ? 4 : 0) | (zz < 0 ? 8 : 0) | (zz >= nc ? 16 : 0);
+        const int* cs = p.cell_start + (wrap_cell(zz, nc) * nc + wrap_cell(yy, nc)) * nc;
+        a0 = cs[xl];
+        a1 = cs[g.cx0];
+        a2 = cs[g.cx0 + g.kx];
+        a3 = cs[xr + 1];
+        l1 = t.wl ? cs[xl + 1] : a1;
+        r0 = t.wr ? cs[xr] : a2;
+        home = b >= 1 && b <= g.ky && c >= 1 && c <= g.kz;
+    }
+    const int nl = l1 - a0, nm = a2 - a1, nr = a3 - r0, cnt = nl + nm + nr;
+    const int inc = wave_scan_incl(cnt), hm = home ? nm : 0, hinc = wave_scan_incl(hm);
+    t.start = lane < nrows ? inc - cnt : 0x7fffffff;
+    t.e1 = inc - cnt + nl;
+    t.e2 = t.e1 + nm;
+    t.d0 = a0 - (inc - cnt);
+    t.d1 = a1 - t.e1;
+    t.d2 = r0 - t.e2;
+    t.hstart = lane < nrows ? hinc - hm : 0x7fffffff;
+    t.total = __builtin_amdgcn_readlane(inc, kWave - 1);
+    t.nh = __builtin_amdgcn_readlane(hinc, kWave - 1);
+    return t;
+}
+
+// For index k of the stretch k0 .. k0 + len - 1 (k0, len the same in every
+// lane), the last row whose start (a value per lane, ascending) is <= k: the
+// row's values of u and v in k's lane, its index in `row`.
+template <bool kRow>
+__device__ __forceinline__ void find_row(int start, int u, int v, int k0, int len, int k, int& uk,
+                                         int& vk, int& row)
+{
+    const uint64_t below = __builtin_amdgcn_ballot_w64(start <= k0);
+    uint64_t in = __builtin_amdgcn_ballot_w64(start < k0 + len) & ~below;
+    const int r0 = (int)__popcll(below) - 1;
+    uk = __builtin_amdgcn_readlane(u, r0);
+    vk = __builtin_amdgcn_readlane(v, r0);
+    row = r0;
+    while (in) {
+        const int r = (int)__ffsll((unsigned long long)in) - 1;
+        in &= in - 1;
+        const bool past = k >= __builtin_amdgcn_readlane(start, r);
+        uk = past ? __builtin_amdgcn_readlane(u, r) : uk;
+        vk = past ? __builtin_amdgcn_readlane(v, r) : vk;
+        if (kRow) row = past ? r : row;
+    }
+}
+
+// Positions of the staged atoms into LDS from the rows (total < cap), as
+// periodic images next to the tile (see stage_atoms; grids of at least 5
+// cells per side), and the sentinel.  With kAux also a second vector per atom.
+// Wave w takes the 64-entry stretches w, w + waves, ..., four at a time.  No
+// barrier: the caller syncs.
+template <bool kAux>
+__device__ __forceinline__ void stage_rows(const KParams& p, const Rows& t, MD_LDS double* p3,
+                                           MD_LDS double* a3, const double* vx, const double* vy,
+                                           const double* vz)
+{
+    constexpr int U = 4;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int w0 = __builtin_amdgcn_readfirstlane((int)threadIdx.x & ~(kWave - 1));
+    const int bd = (int)blockDim.x;
+    for (int c0 = w0; c0 < t.total; c0 += U * bd) {
+        double px[U], py[U], pz[U], qx[U], qy[U], qz[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k0 = c0 + u * bd, k = k0 + lane;
+            if (k0 >= t.total) continue;
+            int d, unused, row;
+            double sx = 0.0, sy = 0.0, sz = 0.0;
+            if (!t.wraps) {
+                find_row<false>(t.start, t.d0, 0, k0, kWave, k, d, unused, row);
+            } else {
+                int fl;
+                find_row<true>(t.start, t.d0, t.fl, k0, kWave, k, d, fl, row);
+                const int e1 = __shfl(t.e1, row, kWave), e2 = __shfl(t.e2, row, kWave);
+                const int d1 = __shfl(t.d1, row, kWave), d2 = __shfl(t.d2, row, kWave);
+                d = k >= e2 ? d2 : (k >= e1 ? d1 : d);
+                sx = t.wl && k < e1 ? -p.L : (t.wr && k >= e2 ? p.L : 0.0);
+                sy = fl & 2 ? -p.L : (fl & 4 ? p.L : 0.0);
+                sz = fl & 8 ? -p.L : (fl & 16 ? p.L : 0.0);
+            }
+            if (k < t.total) {
+                const int j = atom_at(p, k + d);
+                px[u] = p.x[j];
+                py[u] = p.y[j];
+                pz[u] = p.z[j];
+                if (t.wraps) {
+                    px[u] += sx;
+                    py[u] += sy;
+                    pz[u] += sz;
+                }
+                if (kAux) {
+                    qx[u] = vx[j];
+                    qy[u] = vy[j];
+                    qz[u] = vz[j];
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = c0 + u * bd + lane;
+            if (k < t.total) {
+                p3[3 * k] = px[u];
+                p3[3 * k + 1] = py[u];
+                p3[3 * k + 2] = pz[u];
+                if (kAux) {
+                    a3[3 * k] = qx[u];
+                    a3[3 * k + 1] = qy[u];
+                    a3[3 * k + 2] = qz[u];
+                }
+            }
+        }
+    }
+    if (threadIdx.x < 3) {
+        p3[3 * t.total + threadIdx.x] = kSentinel;
+        if (kAux) a3[3 * t.total + threadIdx.x] = 0.0;
     }
 }
 
