@@ -732,7 +732,7 @@ static md_status step_launches(md_ctx* c, hipStream_t s, bool first, int32_t n,
     if (s != c->stream) {  // captured into a graph: never timed, never reordered
         for (int32_t i = 0; i < n; ++i) {
             const int phase = first && i == 0 ? 0 : 1;
-            launch_integrate_pass(k, phase, record_every, s, cells);
+            launch_integrate_pass(k, phase, s, cells);
             finish_and_cells(phase);
             if (nl) neighbors_any(k, fold, s);
             forces_any(k, s, fflags);
@@ -742,7 +742,7 @@ static md_status step_launches(md_ctx* c, hipStream_t s, bool first, int32_t n,
     for (int32_t i = 0; i < n; ++i) {
         const int phase = first && i == 0 ? 0 : 1;
         timed(c, MD_PART_INTEGRATE,
-              [&] { launch_integrate_pass(k, phase, record_every, s, cells); });
+              [&] { launch_integrate_pass(k, phase, s, cells); });
         const bool reorder = layer_reorder_on(c) && (step0 + i + 1) % k.reorder == 0;
         if (small) {  // the finish and the cell build in one launch (counted as cells)
             timed(c, MD_PART_CELLS, [&] { finish_and_cells(phase); });
@@ -761,10 +761,41 @@ static md_status step_launches(md_ctx* c, hipStream_t s, bool first, int32_t n,
     return MD_OK;
 }
 
+// The steps of a system whose integration rides in the force pass
+// (launch_forces_step): an integration pass starts the first step, every body
+// ends one step and starts the next (cells and list if needed, the fused force
+// pass, its finish), and a force pass and an integration pass end the last.
+// The positions change places with the scratch arrays in every body: `flip`
+// says where they are, and the first pass puts them where the last body will
+// leave them in the state arrays.
+static bool fused_steps(const md_ctx* c) { return !c->timing && fused_fits(c->kp); }
+
+static KParams flipped(const KParams& k, bool flip)
+{
+    KParams q = k;
+    if (flip) flip_positions(q);
+    return q;
+}
+
+static void fused_bodies(const md_ctx* c, hipStream_t s, int32_t n, int32_t record_every,
+                         bool& flip)
+{
+    for (int32_t i = 0; i < n; ++i) {
+        const KParams q = flipped(c->kp, flip);
+        launch_cells(q, kFoldCopy, s);
+        launch_neighbors(q, kFoldCopy, s);
+        launch_forces_step(q, s);
+        launch_integrate_finish(q, 1, record_every, s, true);
+        flip = !flip;
+    }
+}
+
 // n_graphs replays of the graph of len steps, captured first if needed.
 // The null stream cannot be captured: then the graph runs on the context's own
 // stream, ordered after and before the bound stream's work by events.
-static md_status step_graphs(md_ctx* c, int32_t len, int32_t n_graphs, int32_t record_every)
+// fused: the steps are fused bodies (fused_bodies), the first from flip.
+static md_status step_graphs(md_ctx* c, int32_t len, int32_t n_graphs, int32_t record_every,
+                             bool fused, bool& flip)
 {
     hipStream_t run = c->stream;
     const bool own = run == nullptr;
@@ -778,11 +809,18 @@ static md_status step_graphs(md_ctx* c, int32_t len, int32_t n_graphs, int32_t r
                 return MD_ERR_HIP;
         run = c->gstream;
     }
-    if (!(c->gexec && c->g_record == record_every && c->g_run == run && c->g_len == len)) {
+    const int kind = fused ? (flip ? 2 : 1) : 0;
+    if (!(c->gexec && c->g_record == record_every && c->g_run == run && c->g_len == len &&
+          c->g_kind == kind)) {
         drop_graph(c);
         if (hipStreamBeginCapture(run, hipStreamCaptureModeThreadLocal) != hipSuccess)
             return MD_ERR_HIP;
-        const md_status st = step_launches(c, run, false, len, record_every, 0);
+        md_status st = MD_OK;
+        bool f = flip;
+        if (fused)
+            fused_bodies(c, run, len, record_every, f);
+        else
+            st = step_launches(c, run, false, len, record_every, 0);
         hipGraph_t g = nullptr;
         const hipError_t ec = hipStreamEndCapture(run, &g);
         if (st != MD_OK) return st;
@@ -793,6 +831,7 @@ static md_status step_graphs(md_ctx* c, int32_t len, int32_t n_graphs, int32_t r
             return MD_ERR_HIP;
         }
         c->g_record = record_every;
+        c->g_kind = kind;
         c->g_len = len;
         c->g_run = run;
     }
@@ -801,6 +840,9 @@ static md_status step_graphs(md_ctx* c, int32_t len, int32_t n_graphs, int32_t r
         return MD_ERR_HIP;
     for (int32_t g = 0; g < n_graphs; ++g)
         if (hipGraphLaunch(c->gexec, run) != hipSuccess) return MD_ERR_HIP;
+    // several replays are of kGraphSteps (even) bodies each: the places are the
+    // same before and after
+    if (fused && len % 2 != 0) flip = !flip;
     if (own && (hipEventRecord(c->gev[1], run) != hipSuccess ||
                 hipStreamWaitEvent(c->stream, c->gev[1], 0) != hipSuccess))
         return MD_ERR_HIP;
@@ -815,13 +857,34 @@ extern "C" md_status md_step(md_ctx* c, int32_t n_steps, int32_t record_every)
     if (n_steps == 0) return MD_OK;
     md_status st;
     const int64_t step0 = c->host_steps;
-    if (c->timing || !c->graph_on || layer_reorder_on(c) || n_steps <= kGraphMin) {
+    bool flip = false;
+    if (fused_steps(c)) {
+        const KParams& k = c->kp;
+        hipStream_t s = c->stream;
+        const int32_t rest = n_steps - 1;
+        flip = rest % 2 != 0;
+        launch_integrate_pass(k, 0, s, false, flip);
+        launch_integrate_finish(k, 0, record_every, s);
+        st = MD_OK;
+        if (!c->graph_on || n_steps <= kGraphMin) {
+            fused_bodies(c, s, rest, record_every, flip);
+        } else {
+            const int32_t len = rest < kGraphSteps ? rest : kGraphSteps, n_graphs = rest / len;
+            st = step_graphs(c, len, n_graphs, record_every, true, flip);
+            if (st == MD_OK) fused_bodies(c, s, rest - n_graphs * len, record_every, flip);
+        }
+        if (st == MD_OK) {
+            launch_cells(k, kFoldCopy, s);
+            launch_neighbors(k, kFoldCopy, s);
+            launch_forces(k, s);
+        }
+    } else if (c->timing || !c->graph_on || layer_reorder_on(c) || n_steps <= kGraphMin) {
         st = step_launches(c, c->stream, true, n_steps, record_every, step0);
     } else {
         const int32_t rest = n_steps - 1;
         const int32_t len = rest < kGraphSteps ? rest : kGraphSteps, n_graphs = rest / len;
         st = step_launches(c, c->stream, true, 1, record_every, step0);
-        if (st == MD_OK) st = step_graphs(c, len, n_graphs, record_every);
+        if (st == MD_OK) st = step_graphs(c, len, n_graphs, record_every, false, flip);
         if (st == MD_OK)
             st = step_launches(c, c->stream, false, rest - n_graphs * len, record_every,
                                step0 + 1 + (int64_t)n_graphs * len);

@@ -171,6 +171,26 @@ md_status upload(md_batch* b)
 void step_sequence(md_batch* b, int32_t n_steps, int32_t record_every)
 {
     const bool nl = b->sh.mode == MD_NEIGHBOR_LIST;
+    bool fused = true;
+    for (const md_ctx* c : b->rep) fused = fused && fused_fits(c->kp);
+    if (fused) {  // the integration in the force pass, as md_step
+        const int32_t rest = n_steps - 1;
+        Batch d = b->dev;
+        launch_integrate_pass(d, b->sh, 0, b->stream, rest % 2 != 0);
+        launch_integrate_finish(d, b->sh, 0, record_every, b->stream, false);
+        d.flip = rest % 2;
+        for (int32_t s = 0; s < n_steps; ++s) {
+            launch_cells(d, b->sh, kFoldCopy, b->stream);
+            launch_neighbors(d, b->sh, kFoldCopy, b->stream);
+            if (s == rest) break;
+            launch_forces_step(d, b->sh, b->stream);
+            launch_integrate_finish(d, b->sh, 1, record_every, b->stream, true);
+            d.flip ^= 1;
+        }
+        launch_forces(d, b->sh, b->stream);
+        launch_integrate(d, b->sh, 2, record_every, b->stream);
+        return;
+    }
     for (int32_t s = 0; s < n_steps; ++s) {
         launch_integrate(b->dev, b->sh, s == 0 ? 0 : 1, record_every, b->stream);
         // the reorder's copy-back folded into the list build

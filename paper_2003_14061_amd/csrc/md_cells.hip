@@ -47,7 +47,9 @@ __global__ void k_clear(B b)
         d->flags = 0;
         d->max_occ = 0;
         d->max_nl = 0;
+        d->record = 0;
         for (int k = 0; k < 8; ++k) d->obs[k] = 0.0;
+        for (int k = 0; k < kDmaxSlots; ++k) d->dmax_slot[k] = 0;
     }
 }
 
@@ -178,8 +180,11 @@ __device__ __forceinline__ void scatter_atom(const KParams& p, int i)
 // slot-order position q counts the members of its cell with a smaller id
 // (ids are distinct); that count is its place.  With kPermute the atom's
 // data go to that place in the scratch arrays (the permutation into cell
-// order, scattered from the atom rather than gathered by a second pass).
-template <typename F, bool kPermute>
+// order, scattered from the atom rather than gathered by a second pass):
+// P_NONE nothing, P_STATE all but the forces, P_ALL the forces (type F) too.
+enum Permute { P_NONE, P_STATE, P_ALL };
+
+template <typename F, Permute kPermute>
 __device__ __forceinline__ void sort_slot(const KParams& p, int q)
 {
     const int32_t* ids = p.tmp + p.n;  // ids in slot order (scatter_atom)
@@ -199,9 +204,11 @@ __device__ __forceinline__ void sort_slot(const KParams& p, int q)
         p.svx[d] = p.vx[s];
         p.svy[d] = p.vy[s];
         p.svz[d] = p.vz[s];
-        reinterpret_cast<F*>(p.sfx)[d] = static_cast<const F*>(p.fx)[s];
-        reinterpret_cast<F*>(p.sfy)[d] = static_cast<const F*>(p.fy)[s];
-        reinterpret_cast<F*>(p.sfz)[d] = static_cast<const F*>(p.fz)[s];
+        if (kPermute == P_ALL) {
+            reinterpret_cast<F*>(p.sfx)[d] = static_cast<const F*>(p.fx)[s];
+            reinterpret_cast<F*>(p.sfy)[d] = static_cast<const F*>(p.fy)[s];
+            reinterpret_cast<F*>(p.sfz)[d] = static_cast<const F*>(p.fz)[s];
+        }
         p.sid[d] = key;
         p.scell[d] = c;
     }
@@ -217,7 +224,7 @@ __global__ void k_scatter(B b, int force)
         scatter_atom(p, i);
 }
 
-template <typename F, class B, bool kPermute>
+template <typename F, class B, Permute kPermute>
 __global__ void k_cellsort(B b, int force)
 {
     Wg wg;
@@ -233,7 +240,7 @@ __global__ void k_cellsort(B b, int force)
 // next inside the workgroup).  kFinish (cells-only steps, which rebuild
 // every step): the workgroup first finishes the integration pass before it
 // (finish_step), in place of k_int_finish.
-template <typename F, class B, bool kPermute, bool kFinish>
+template <typename F, class B, Permute kPermute, bool kFinish>
 __global__ __launch_bounds__(kScanThreads) void k_sort_small(B b, int force, int phase,
                                                              int record_every)
 {
@@ -242,7 +249,7 @@ __global__ __launch_bounds__(kScanThreads) void k_sort_small(B b, int force, int
     if (!b.fetch(G_ONE, wg, p)) return;
     if (kFinish) {
         __shared__ double red[(kScanThreads / kWave) * 5];
-        finish_step(p, phase, record_every, red);
+        finish_step(p, phase, record_every, false, red);
         __syncthreads();
     } else if (!rebuild_on(p, force)) {
         return;
@@ -263,13 +270,13 @@ __global__ __launch_bounds__(kScanThreads) void k_sort_small(B b, int force, int
 // systems whose tables fit (sort_lds_bytes).
 constexpr int kSortAtomBits = 14;  // atoms of a small system: at most kSortSmall = 2^14
 
-template <typename F, bool kPermute>
+template <bool kPermute>
 __global__ __launch_bounds__(kScanThreads) void k_sort_lds(Single b, int phase, int record_every)
 {
     const KParams& p = b.p;
     {
         __shared__ double red[(kScanThreads / kWave) * 5];
-        finish_step(p, phase, record_every, red);
+        finish_step(p, phase, record_every, false, red);
         __syncthreads();
     }
     extern __shared__ int lds[];
@@ -300,9 +307,6 @@ __global__ __launch_bounds__(kScanThreads) void k_sort_lds(Single b, int phase, 
             p.svx[d] = p.vx[s];
             p.svy[d] = p.vy[s];
             p.svz[d] = p.vz[s];
-            reinterpret_cast<F*>(p.sfx)[d] = static_cast<const F*>(p.fx)[s];
-            reinterpret_cast<F*>(p.sfy)[d] = static_cast<const F*>(p.fy)[s];
-            reinterpret_cast<F*>(p.sfz)[d] = static_cast<const F*>(p.fz)[s];
             p.sid[d] = key;
             p.scell[d] = c;
         }
@@ -356,23 +360,28 @@ static void cells_seq(const B& b, const LaunchShape& sh, int flags, hipStream_t 
     if (n_small) {  // one system of at most kSortSmall atoms
         const dim3 one(1), t(kScanThreads);
         if (!sh.reorder)
-            hipLaunchKernelGGL((k_sort_small<double, B, false, false>), one, t, 0, s, b, force,
+            hipLaunchKernelGGL((k_sort_small<double, B, P_NONE, false>), one, t, 0, s, b, force,
+                               0, 0);
+        else if (!copy)
+            hipLaunchKernelGGL((k_sort_small<double, B, P_STATE, false>), one, t, 0, s, b, force,
                                0, 0);
         else if (sh.precision == MD_FP64)
-            hipLaunchKernelGGL((k_sort_small<double, B, true, false>), one, t, 0, s, b, force, 0,
+            hipLaunchKernelGGL((k_sort_small<double, B, P_ALL, false>), one, t, 0, s, b, force, 0,
                                0);
         else
-            hipLaunchKernelGGL((k_sort_small<float, B, true, false>), one, t, 0, s, b, force, 0,
+            hipLaunchKernelGGL((k_sort_small<float, B, P_ALL, false>), one, t, 0, s, b, force, 0,
                                0);
     } else {
         hipLaunchKernelGGL(k_scan<B>, dim3(sh.grid[G_ONE]), dim3(kScanThreads), 0, s, b, force);
         hipLaunchKernelGGL(k_scatter<B>, atoms, blk, 0, s, b, force);
         if (!sh.reorder)
-            hipLaunchKernelGGL((k_cellsort<double, B, false>), atoms, blk, 0, s, b, force);
+            hipLaunchKernelGGL((k_cellsort<double, B, P_NONE>), atoms, blk, 0, s, b, force);
+        else if (!copy)
+            hipLaunchKernelGGL((k_cellsort<double, B, P_STATE>), atoms, blk, 0, s, b, force);
         else if (sh.precision == MD_FP64)
-            hipLaunchKernelGGL((k_cellsort<double, B, true>), atoms, blk, 0, s, b, force);
+            hipLaunchKernelGGL((k_cellsort<double, B, P_ALL>), atoms, blk, 0, s, b, force);
         else
-            hipLaunchKernelGGL((k_cellsort<float, B, true>), atoms, blk, 0, s, b, force);
+            hipLaunchKernelGGL((k_cellsort<float, B, P_ALL>), atoms, blk, 0, s, b, force);
     }
     if (sh.reorder && copy) {
         if (sh.precision == MD_FP64)
@@ -405,24 +414,17 @@ void launch_sort_small_finish(const KParams& p, int phase, int record_every, hip
     const Single b{p};
     const size_t lds = sort_lds_bytes(p);
     if (lds) {
-        if (!p.reorder)
-            hipLaunchKernelGGL((k_sort_lds<double, false>), one, t, lds, s, b, phase,
-                               record_every);
-        else if (p.precision == MD_FP64)
-            hipLaunchKernelGGL((k_sort_lds<double, true>), one, t, lds, s, b, phase, record_every);
+        if (p.reorder)
+            hipLaunchKernelGGL(k_sort_lds<true>, one, t, lds, s, b, phase, record_every);
         else
-            hipLaunchKernelGGL((k_sort_lds<float, true>), one, t, lds, s, b, phase, record_every);
-        return;
+            hipLaunchKernelGGL(k_sort_lds<false>, one, t, lds, s, b, phase, record_every);
+    } else if (p.reorder) {
+        hipLaunchKernelGGL((k_sort_small<double, Single, P_STATE, true>), one, t, 0, s, b, 1,
+                           phase, record_every);
+    } else {
+        hipLaunchKernelGGL((k_sort_small<double, Single, P_NONE, true>), one, t, 0, s, b, 1,
+                           phase, record_every);
     }
-    if (!p.reorder)
-        hipLaunchKernelGGL((k_sort_small<double, Single, false, true>), one, t, 0, s, b, 1, phase,
-                           record_every);
-    else if (p.precision == MD_FP64)
-        hipLaunchKernelGGL((k_sort_small<double, Single, true, true>), one, t, 0, s, b, 1, phase,
-                           record_every);
-    else
-        hipLaunchKernelGGL((k_sort_small<float, Single, true, true>), one, t, 0, s, b, 1, phase,
-                           record_every);
 }
 
 void launch_clear(const Batch& b, const LaunchShape& sh, hipStream_t s) { clear_seq(b, sh, s); }

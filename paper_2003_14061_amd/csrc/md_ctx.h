@@ -63,6 +63,7 @@ struct md_ctx {
     hipGraphExec_t gexec = nullptr;
     int g_record = -1;                     // record_every the graph was captured with
     int g_len = 0;                         // steps in the graph
+    int g_kind = 0;                        // 0: plain steps, 1 / 2: fused bodies from flip 0 / 1
     hipStream_t g_run = nullptr;           // stream it was captured on
     hipStream_t gstream = nullptr;         // own stream, when the bound one is the null stream
     hipEvent_t gev[2] = {nullptr, nullptr};

@@ -239,6 +239,36 @@ __device__ __forceinline__ void block_sum(double (&v)[K], double* red)
     __syncthreads();
 }
 
+// Sum K values and take the maximum of m >= 0 across the workgroup; both valid
+// in thread 0.  red must hold (blockDim.x / 64) * (K + 1) doubles of LDS.
+template <int K>
+__device__ __forceinline__ void block_sum_max(double (&v)[K], double& m, double* red)
+{
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    const int nw = blockDim.x / kWave;
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = wave_sum(v[k]);
+    m = wave_max(m);
+    if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) red[wid * (K + 1) + k] = v[k];
+        red[wid * (K + 1) + K] = m;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            double t = 0.0;
+            for (int w = 0; w < nw; ++w) t += red[w * (K + 1) + k];
+            v[k] = t;
+        }
+        for (int w = 1; w < nw; ++w) {
+            const double t = red[w * (K + 1) + K];
+            m = t > m ? t : m;
+        }
+    }
+}
+
 // A value another workgroup of the running kernel published before its
 // release in last_block: an agent-scope atomic load, which reads the
 // coherence point past this XCD's L2 without invalidating it.
@@ -324,18 +354,14 @@ __device__ __forceinline__ KParams scratch_view(const KParams& p)
     q.vx = p.svx; q.svx = p.vx;
     q.vy = p.svy; q.svy = p.vy;
     q.vz = p.svz; q.svz = p.vz;
-    // the force scratch arrays are typed double but hold the force type
-    q.fx = p.sfx; q.sfx = static_cast<double*>(p.fx);
-    q.fy = p.sfy; q.sfy = static_cast<double*>(p.fy);
-    q.fz = p.sfz; q.sfz = static_cast<double*>(p.fz);
     q.id = p.sid; q.sid = p.id;
     q.cell_of = p.scell; q.scell = p.cell_of;
     return q;
 }
 
-// Atom at slot k, over scratch_view: its sorted data into the state (the
-// forces too unless kForces is false, for a pass that writes them anew).
-template <bool kCopy, bool kForces = true>
+// Atom at slot k, over scratch_view: its sorted data into the state, except
+// the forces, which the force pass of the same step writes anew.
+template <bool kCopy>
 __device__ __forceinline__ void copy_home(const KParams& q, int k)
 {
     if (!kCopy) return;
@@ -345,16 +371,6 @@ __device__ __forceinline__ void copy_home(const KParams& q, int k)
     q.svx[k] = q.vx[k];
     q.svy[k] = q.vy[k];
     q.svz[k] = q.vz[k];
-    if (!kForces) {
-    } else if (q.precision == MD_FP64) {
-        q.sfx[k] = static_cast<const double*>(q.fx)[k];
-        q.sfy[k] = static_cast<const double*>(q.fy)[k];
-        q.sfz[k] = static_cast<const double*>(q.fz)[k];
-    } else {
-        reinterpret_cast<float*>(q.sfx)[k] = static_cast<const float*>(q.fx)[k];
-        reinterpret_cast<float*>(q.sfy)[k] = static_cast<const float*>(q.fy)[k];
-        reinterpret_cast<float*>(q.sfz)[k] = static_cast<const float*>(q.fz)[k];
-    }
     q.sid[k] = q.id[k];
     q.scell[k] = q.cell_of[k];
     q.order[k] = k;

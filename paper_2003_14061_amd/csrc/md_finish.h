@@ -47,36 +47,46 @@ __device__ __forceinline__ double finish_max(const double* part, int nb, int str
     return m;
 }
 
+// Whether the history asks for step (record_every > 0: every multiple of it).
+__device__ __forceinline__ bool recorded(int64_t step, int record_every)
+{
+    if (record_every <= 1) return record_every == 1;
+    if (step < 0x7fffffff) return (uint32_t)step % (uint32_t)record_every == 0;
+    return step % record_every == 0;
+}
+
 // Finish a completed step: count it, and on steps the history asks for, sum
-// U, W (last force pass) and K, P (this kernel's n_wg partials) and append
-// them.
+// U, W (last force pass) and K, P (the partials of the integration pass, or
+// with fused those of the fused force pass: component c of tile t at
+// fpart[(2 + c) n_tiles + t]) and append them.
 __device__ __forceinline__ void record_step(const KParams& p, int n_wg, int record_every,
-                                            double* red)
+                                            bool fused, double* red)
 {
     DevState* dd = p.dev;
     const int64_t step = dd->step + 1;
     __syncthreads();
     if (threadIdx.x == 0) dd->step = step;
-    if (!(record_every > 0 && step % record_every == 0)) return;
+    if (!recorded(step, record_every)) return;
     double U = finish_sum<kFinishThreads>(p.fpart, p.nblk_force, 2, 0, red);
     double W = finish_sum<kFinishThreads>(p.fpart, p.nblk_force, 2, 1, red);
     if (p.bonded_on) {
         U += finish_sum<kFinishThreads>(p.bpart, p.nblk_bonded, 2, 0, red);
         W += finish_sum<kFinishThreads>(p.bpart, p.nblk_bonded, 2, 1, red);
     }
-    const double K = finish_sum<kFinishThreads>(p.ipart, n_wg, 8, 0, red);
-    const double Px = finish_sum<kFinishThreads>(p.ipart, n_wg, 8, 1, red);
-    const double Py = finish_sum<kFinishThreads>(p.ipart, n_wg, 8, 2, red);
-    const double Pz = finish_sum<kFinishThreads>(p.ipart, n_wg, 8, 3, red);
+    double kp[4];
+    for (int c = 0; c < 4; ++c)
+        kp[c] = fused ? finish_sum<kFinishThreads>(p.fpart + (2 + c) * (int64_t)p.n_tiles,
+                                                   p.n_tiles, 1, 0, red)
+                      : finish_sum<kFinishThreads>(p.ipart, n_wg, 8, c, red);
     if (threadIdx.x == 0) {
         md_record* r = p.hist + (dd->hist_count % kHistCap);
         r->step = step;
         r->U = U;
-        r->K = 0.5 * p.mass * K;
+        r->K = 0.5 * p.mass * kp[0];
         r->W = W;
-        r->P[0] = p.mass * Px;
-        r->P[1] = p.mass * Py;
-        r->P[2] = p.mass * Pz;
+        r->P[0] = p.mass * kp[1];
+        r->P[1] = p.mass * kp[2];
+        r->P[2] = p.mass * kp[3];
         r->dmax = sqrt(dd->dmax2);
         r->rebuilt = dd->rebuild;
         r->pad = 0;
@@ -87,18 +97,34 @@ __device__ __forceinline__ void record_step(const KParams& p, int n_wg, int reco
 // The end of an integration pass: count the step and record it (phase >= 1),
 // and from the largest displacement decide whether the cells and list are
 // rebuilt before the next force pass (phase <= 1).  By one workgroup of at
-// least kFinishThreads threads (red: LDS, (blockDim / 64) * 5 doubles).
+// least kFinishThreads threads (red: LDS, (blockDim / 64) * 5 doubles).  fused:
+// the pass was a fused force pass (launch_forces_step).
 __device__ __forceinline__ void finish_step(const KParams& p, int phase, int record_every,
-                                            double* red)
+                                            bool fused, double* red)
 {
     const int n_wg = grid_of(p, G_INTEGRATE);
-    if (phase >= 1) record_step(p, n_wg, record_every, red);
+    if (phase >= 1) record_step(p, n_wg, record_every, fused, red);
     if (phase <= 1) {
         __shared__ int rb_all;
-        const double m = finish_max<kFinishThreads>(p.ipart, n_wg, 8, 4, red);
+        double m = 0.0;
+        if (fused) {
+            if (threadIdx.x < kWave) {
+                unsigned long long* slot = p.dev->dmax_slot;
+                double v = 0.0;
+                if (threadIdx.x < kDmaxSlots) {
+                    v = __longlong_as_double((long long)slot[threadIdx.x]);
+                    slot[threadIdx.x] = 0;
+                }
+                m = wave_max(v);
+            }
+        } else {
+            m = finish_max<kFinishThreads>(p.ipart, n_wg, 8, 4, red);
+        }
         if (threadIdx.x == 0) {
             DevState* d = p.dev;
             d->dmax2 = m;
+            // whether the step that the next fused force pass ends is recorded
+            d->record = recorded(d->step + 1, record_every) ? 1 : 0;
             const int rb = p.mode == MD_CELLS_ONLY ? 1 : (m > p.disp_thr2 ? 1 : 0);
             d->rebuild = rb;
             if (rb) d->n_rebuilds += 1;

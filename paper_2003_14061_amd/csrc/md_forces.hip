@@ -170,26 +170,94 @@ __global__ void k_zero_forces(B b)
     }
 }
 
-// One home atom's sums, finished: its force written, its energy and half
-// virial added to e.
+// What a force pass does with each home atom's sums, and what it sums over
+// the atoms.  kStep: the integration pass follows in the same kernel
+// (launch_forces_step), else the force is written.  kEnergy: energy and virial
+// too (and, with kStep, the kinetic sums of a recorded step).
+template <typename F, bool kStep, bool kEnergy>
+struct HomeEnd {
+    using Sums = Lean<F>;
+    double e[2] = {0.0, 0.0};             // U, W
+    double k[4] = {0.0, 0.0, 0.0, 0.0};   // v^2, Px, Py, Pz (kStep)
+    double dmax2 = 0.0;                   // largest squared displacement (kStep)
+
+    __device__ __forceinline__ void operator()(const KParams& p, const Sums& a, int i, double xi,
+                                               double yi, double zi)
+    {
+        F fx, fy, fz;
+        double ui = 0.0, wi;
+        lean_finish(p, a, fx, fy, fz, ui, wi);
+        e[0] += ui;
+        e[1] += wi;
+        finish(p, fx, fy, fz, ui, i, xi, yi, zi);
+    }
+    __device__ __forceinline__ void finish(const KParams& p, F fx, F fy, F fz, double ui, int i,
+                                           double xi, double yi, double zi)
+    {
+        if (kStep) {
+            double vx = p.vx[i], vy = p.vy[i], vz = p.vz[i];
+            const double rx = p.xr[i], ry = p.yr[i], rz = p.zr[i];
+            const double gx = (double)fx, gy = (double)fy, gz = (double)fz;
+            // second half kick of the finished step, then first half kick and
+            // drift of the next, as k_integrate
+            vx = kick(vx, p.hdt, gx);
+            vy = kick(vy, p.hdt, gy);
+            vz = kick(vz, p.hdt, gz);
+            if (kEnergy) {
+                k[0] += (vx * vx + vy * vy) + vz * vz;
+                k[1] += vx;
+                k[2] += vy;
+                k[3] += vz;
+            }
+            vx = kick(vx, p.hdt, gx);
+            vy = kick(vy, p.hdt, gy);
+            vz = kick(vz, p.hdt, gz);
+            const double x = drift(xi, p.dt, vx), y = drift(yi, p.dt, vy),
+                         z = drift(zi, p.dt, vz);
+            p.sx[i] = x;
+            p.sy[i] = y;
+            p.sz[i] = z;
+            p.vx[i] = vx;
+            p.vy[i] = vy;
+            p.vz[i] = vz;
+            const double d2 = dist2(minimg(x - rx, p.L, p.invL), minimg(y - ry, p.L, p.invL),
+                                    minimg(z - rz, p.L, p.invL));
+            dmax2 = d2 > dmax2 ? d2 : dmax2;
+        } else {
+            static_cast<F*>(p.fx)[i] = fx;
+            static_cast<F*>(p.fy)[i] = fy;
+            static_cast<F*>(p.fz)[i] = fz;
+        }
+        if (!isfinite(ui + (double)fx + (double)fy + (double)fz))
+            atomicOr(&p.dev->flags, (int)MD_FLAG_NONFINITE);
+    }
+};
+
+// Without the energies (a non-finite energy shows in the force: it needs
+// sr6 (sr6 - 1/2) past the range, a factor of every force component).
 template <typename F>
-__device__ __forceinline__ void home_finish(const KParams& p, const LeanOf<F>& a, int slot_i,
-                                            double (&e)[2])
+struct HomeEnd<F, true, false> : HomeEnd<F, true, true> {
+    using Sums = LeanForce<F>;
+    __device__ __forceinline__ void operator()(const KParams& p, const Sums& a, int i, double xi,
+                                               double yi, double zi)
+    {
+        const F s = (F)p.eps48;
+        this->finish(p, s * a.fx, s * a.fy, s * a.fz, 0.0, i, xi, yi, zi);
+    }
+};
+
+template <int LANES, typename T>
+__device__ __forceinline__ void group_sum(LeanForce<T>& a)
 {
-    F fx, fy, fz;
-    double ui, wi;
-    lean_finish(p, a, fx, fy, fz, ui, wi);
-    static_cast<F*>(p.fx)[slot_i] = fx;
-    static_cast<F*>(p.fy)[slot_i] = fy;
-    static_cast<F*>(p.fz)[slot_i] = fz;
-    e[0] += ui;
-    e[1] += wi;
-    if (!isfinite(ui + (double)fx + (double)fy + (double)fz))
-        atomicOr(&p.dev->flags, (int)MD_FLAG_NONFINITE);
+    if (LANES > 1) {
+        a.fx = lane_group_sum<LANES>(a.fx);
+        a.fy = lane_group_sum<LANES>(a.fy);
+        a.fz = lane_group_sum<LANES>(a.fz);
+    }
 }
 
 template <int LANES, typename T>
-__device__ __forceinline__ void lean_group_sum(Lean<T>& a)
+__device__ __forceinline__ void group_sum(Lean<T>& a)
 {
     if (LANES > 1) {
         a.fx = lane_group_sum<LANES>(a.fx);
@@ -208,9 +276,8 @@ __device__ __forceinline__ void lean_group_sum(Lean<T>& a)
 // ones; against the tables (four barriers, a search per staged atom) it
 // measured 223 against 241 us at 2.048M LJ atoms, 16.5 against 19.2 us at
 // 256 000 WCA atoms and 56 against 65 us for 64 replicas (1.03M atoms).
-template <typename F, int LANES>
-__device__ __forceinline__ void forces_rows(const KParams& p, const Rows& t, char* smem,
-                                            double (&e)[2])
+template <int LANES, class End>
+__device__ __forceinline__ void forces_rows(const KParams& p, const Rows& t, char* smem, End& end)
 {
     MD_LDS double* p3 = (MD_LDS double*)smem;
     constexpr int kPer = kWave / LANES;  // home atoms of a wave
@@ -239,24 +306,24 @@ __device__ __forceinline__ void forces_rows(const KParams& p, const Rows& t, cha
         if (!staged) __syncthreads();
         staged = true;
         if (h0 >= t.nh) break;
-        LeanOf<F> a;
+        typename End::Sums a;
+        double xi = 0.0, yi = 0.0, zi = 0.0;
         if (h < t.nh) {
-            double xi, yi, zi;
             lds_xyz(p3, eh, xi, yi, zi);
-            ForceOp<LeanOf<F>> op{p, a};
+            ForceOp<typename End::Sums> op{p, a};
             walk_staged<LANES>(p, p3, slot_i, sub, cnt, next, xi, yi, zi, op);
         }
-        lean_group_sum<LANES>(a);
-        if (h < t.nh && sub == 0) home_finish<F>(p, a, slot_i, e);
+        group_sum<LANES>(a);
+        if (h < t.nh && sub == 0) end(p, a, slot_i, xi, yi, zi);
     }
 }
 
 // Any other tile (more than 64 staged rows, atoms past the LDS capacity, or a
 // grid of fewer than 5 cells per side, whose pairs take the minimum image by
 // rounding): through the cell tables in LDS.
-template <typename F, int LANES>
+template <int LANES, class End>
 __device__ __forceinline__ void forces_tables(const KParams& p, const Tile& g, char* smem,
-                                              double (&e)[2])
+                                              End& end)
 {
     Stage s = stage_layout(p, smem);
     stage_tables(p, g, s);
@@ -268,15 +335,15 @@ __device__ __forceinline__ void forces_tables(const KParams& p, const Tile& g, c
     const int sub = threadIdx.x % LANES;
     for (int hb = 0; hb < nh; hb += per_pass) {
         const int h = hb + threadIdx.x / LANES;
-        LeanOf<F> a;
+        typename End::Sums a;
         int slot_i = 0;
+        double xi = 0.0, yi = 0.0, zi = 0.0;
         if (h < nh) {
             int eh, pos;
             home_atom(s, h, eh, pos);
             slot_i = atom_at(p, pos);
-            double xi, yi, zi;
             home_position(p, s, eh, slot_i, xi, yi, zi);
-            ForceOp<LeanOf<F>> op{p, a};
+            ForceOp<typename End::Sums> op{p, a};
             // the lane's list-row offset is formed here for each pass: hoisted out
             // of the pass loop it is a 64-bit value live across the whole kernel
             // (the empty asm hides that sub is the same in every pass)
@@ -284,15 +351,29 @@ __device__ __forceinline__ void forces_tables(const KParams& p, const Tile& g, c
             asm volatile("" : "+v"(sub_p));
             walk_home<LANES>(p, s, mode, slot_i, sub_p, p.nl_count[slot_i], xi, yi, zi, op);
         }
-        lean_group_sum<LANES>(a);
-        if (h < nh && sub == 0) home_finish<F>(p, a, slot_i, e);
+        group_sum<LANES>(a);
+        if (h < nh && sub == 0) end(p, a, slot_i, xi, yi, zi);
     }
+}
+
+// One tile by whichever way it takes.
+template <int LANES, class End>
+__device__ __forceinline__ void forces_tile(const KParams& p, const Wg& wg, char* smem, End& end)
+{
+    const Tile g = tile_of(p, xcd_tile(wg.id, wg.n));
+    bool rows = rows_fit(p) && p.nc >= 5;
+    if (rows) {
+        const Rows t = row_table(p, g);
+        rows = t.total < p.scap;
+        if (rows) forces_rows<LANES>(p, t, smem, end);
+    }
+    if (!rows) forces_tables<LANES>(p, g, smem, end);
 }
 
 // Six waves per SIMD (at most 80 VGPRs): three workgroups of the default
 // shape fit a CU by LDS, and the compiler's own allocation otherwise crosses
 // the five-wave line.
-template <typename F, typename Acc, int LANES, class B>
+template <typename F, int LANES, class B>
 __global__ __attribute__((amdgpu_waves_per_eu(6))) void k_forces_tiles(B b)
 {
     Wg wg;
@@ -300,20 +381,53 @@ __global__ __attribute__((amdgpu_waves_per_eu(6))) void k_forces_tiles(B b)
     if (!b.fetch(G_TILES, wg, p)) return;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     __shared__ double red[(1024 / kWave) * 2];
-    const Tile g = tile_of(p, xcd_tile(wg.id, wg.n));
-    double e[2] = {0.0, 0.0};
-    bool rows = rows_fit(p) && p.nc >= 5;
-    if (rows) {
-        const Rows t = row_table(p, g);
-        rows = t.total < p.scap;
-        if (rows) forces_rows<F, LANES>(p, t, smem, e);
-    }
-    if (!rows) forces_tables<F, LANES>(p, g, smem, e);
-    block_sum<2>(e, red);
+    HomeEnd<F, false, true> end;
+    forces_tile<LANES>(p, wg, smem, end);
+    block_sum<2>(end.e, red);
     if (threadIdx.x == 0) {
-        p.fpart[2 * wg.id] = e[0];
-        p.fpart[2 * wg.id + 1] = e[1];
+        p.fpart[2 * wg.id] = end.e[0];
+        p.fpart[2 * wg.id + 1] = end.e[1];
     }
+}
+
+// The force pass with the integration pass that follows it (see
+// launch_forces_step).  The integration alone is bound by HBM (144 B per atom)
+// and the force pass by VALU issue, so together the integration's traffic,
+// less the forces and the reread positions (96 B per atom), hides under the pair
+// walk: 238 us against 223 + 47 us at 2.048M LJ atoms, 19.3 against 16.5 + 8.4 us
+// at 256 000 WCA atoms, 69 against 56 + 25 us for 64 replicas.  Energies, virial and kinetic sums only when the history
+// asks for the step (DevState::record, set by the finish before this launch);
+// the largest displacement always.
+template <typename F, int LANES, class B>
+__global__ __attribute__((amdgpu_waves_per_eu(6))) void k_forces_step(B b)
+{
+    Wg wg;
+    KParams p;
+    if (!b.fetch(G_TILES, wg, p)) return;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    __shared__ double red[(1024 / kWave) * 7];
+    double dmax2;
+    if (p.dev->record) {
+        HomeEnd<F, true, true> end;
+        forces_tile<LANES>(p, wg, smem, end);
+        double v[6] = {end.e[0], end.e[1], end.k[0], end.k[1], end.k[2], end.k[3]};
+        dmax2 = end.dmax2;
+        block_sum_max<6>(v, dmax2, red);
+        if (threadIdx.x == 0) {
+            p.fpart[2 * wg.id] = v[0];
+            p.fpart[2 * wg.id + 1] = v[1];
+            for (int c = 0; c < 4; ++c) p.fpart[(2 + c) * (int64_t)p.n_tiles + wg.id] = v[2 + c];
+        }
+    } else {
+        HomeEnd<F, true, false> end;
+        forces_tile<LANES>(p, wg, smem, end);
+        double v[1] = {0.0};
+        dmax2 = end.dmax2;
+        block_sum_max<1>(v, dmax2, red);
+    }
+    if (threadIdx.x == 0)
+        atomicMax(&p.dev->dmax_slot[wg.id % kDmaxSlots],
+                  (unsigned long long)__double_as_longlong(dmax2));
 }
 
 // ---- cells-only mode ----
@@ -373,7 +487,7 @@ __global__ void k_forces_cells(B b)
     if (i < p.n && sub == 0) {
         F fx, fy, fz;
         lean_finish(p, a, fx, fy, fz, e[0], e[1]);
-        copy_home<kCopy, false>(p, i);
+        copy_home<kCopy>(p, i);
         fout[0][i] = fx;
         fout[1][i] = fy;
         fout[2][i] = fz;
@@ -411,10 +525,23 @@ static void tiles_seq(const B& b, const LaunchShape& sh, hipStream_t s)
     const dim3 g(sh.grid[G_TILES]), t(sh.force_block);
     const size_t lds = sh.force_lds;
     switch (sh.force_lanes) {
-        case 8: hipLaunchKernelGGL((k_forces_tiles<F, Acc, 8, B>), g, t, lds, s, b); break;
-        case 2: hipLaunchKernelGGL((k_forces_tiles<F, Acc, 2, B>), g, t, lds, s, b); break;
-        case 4: hipLaunchKernelGGL((k_forces_tiles<F, Acc, 4, B>), g, t, lds, s, b); break;
-        default: hipLaunchKernelGGL((k_forces_tiles<F, Acc, 1, B>), g, t, lds, s, b); break;
+        case 8: hipLaunchKernelGGL((k_forces_tiles<F, 8, B>), g, t, lds, s, b); break;
+        case 2: hipLaunchKernelGGL((k_forces_tiles<F, 2, B>), g, t, lds, s, b); break;
+        case 4: hipLaunchKernelGGL((k_forces_tiles<F, 4, B>), g, t, lds, s, b); break;
+        default: hipLaunchKernelGGL((k_forces_tiles<F, 1, B>), g, t, lds, s, b); break;
+    }
+}
+
+template <typename F, class B>
+static void step_seq(const B& b, const LaunchShape& sh, hipStream_t s)
+{
+    const dim3 g(sh.grid[G_TILES]), t(sh.force_block);
+    const size_t lds = sh.force_lds;
+    switch (sh.force_lanes) {
+        case 8: hipLaunchKernelGGL((k_forces_step<F, 8, B>), g, t, lds, s, b); break;
+        case 2: hipLaunchKernelGGL((k_forces_step<F, 2, B>), g, t, lds, s, b); break;
+        case 4: hipLaunchKernelGGL((k_forces_step<F, 4, B>), g, t, lds, s, b); break;
+        default: hipLaunchKernelGGL((k_forces_step<F, 1, B>), g, t, lds, s, b); break;
     }
 }
 
@@ -473,5 +600,22 @@ void launch_forces(const KParams& p, hipStream_t s, int flags)
 }
 
 void launch_forces(const Batch& b, const LaunchShape& sh, hipStream_t s) { forces_seq(b, sh, s); }
+
+void launch_forces_step(const KParams& p, hipStream_t s)
+{
+    const Single b{p};
+    if (p.precision == MD_FP64)
+        step_seq<double>(b, shape_of(p), s);
+    else
+        step_seq<float>(b, shape_of(p), s);
+}
+
+void launch_forces_step(const Batch& b, const LaunchShape& sh, hipStream_t s)
+{
+    if (sh.precision == MD_FP64)
+        step_seq<double>(b, sh, s);
+    else
+        step_seq<float>(b, sh, s);
+}
 
 }  // namespace md

@@ -11,6 +11,10 @@
 // paper refreshes "at intervals of several time steps", section 2.3, from a
 // bound on the maximal velocity; here the bound is the displacement itself).
 //
+// Between the steps of one call the tiled list pipeline with reorder does
+// this pass inside the force pass instead (k_forces_step), with the same
+// operations per atom.
+//
 // Reductions (section 2.3, F2): each integration workgroup writes its
 // partial sums, and k_int_finish, one workgroup per system launched right
 // after, sums them in workgroup order and publishes the result on the
@@ -28,7 +32,7 @@ namespace md {
 // folds the positions into [0, L) and bins them (cell and slot, as k_bin), so
 // that the cell build that follows starts at the scan.
 template <typename F, class B, bool kBin>
-__global__ __launch_bounds__(kIntThreads) void k_integrate(B b, int phase, int record_every)
+__global__ __launch_bounds__(kIntThreads) void k_integrate(B b, int phase, int to_scratch)
 {
     Wg wg;
     KParams p;
@@ -37,6 +41,9 @@ __global__ __launch_bounds__(kIntThreads) void k_integrate(B b, int phase, int r
     const F* fx = static_cast<const F*>(p.fx);
     const F* fy = static_cast<const F*>(p.fy);
     const F* fz = static_cast<const F*>(p.fz);
+    double* const ox = to_scratch ? p.sx : p.x;
+    double* const oy = to_scratch ? p.sy : p.y;
+    double* const oz = to_scratch ? p.sz : p.z;
     double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};  // v^2, Px, Py, Pz, (unused)
     double dmax2 = 0.0;
     const int stride = wg.n * blockDim.x;
@@ -85,9 +92,9 @@ __global__ __launch_bounds__(kIntThreads) void k_integrate(B b, int phase, int r
                     c = cell_of_pos(x, y, z, p);
                     p.cell_of[i] = c;
                 }
-                p.x[i] = x;
-                p.y[i] = y;
-                p.z[i] = z;
+                ox[i] = x;
+                oy[i] = y;
+                oz[i] = z;
                 if (track) {
                     const double d2 =
                         dist2(minimg(x - rx, p.L, p.invL), minimg(y - ry, p.L, p.invL),
@@ -126,13 +133,13 @@ __global__ __launch_bounds__(kIntThreads) void k_integrate(B b, int phase, int r
 
 // The end of an integration pass (one workgroup per system, see finish_step).
 template <class B>
-__global__ __launch_bounds__(kFinishThreads) void k_int_finish(B b, int phase, int record_every)
+__global__ __launch_bounds__(kFinishThreads) void k_int_finish(B b, int phase, int record_every, int fused)
 {
     Wg wg;
     KParams p;
     if (!b.fetch(G_ONE, wg, p)) return;
     __shared__ double red[(kFinishThreads / kWave) * 5];
-    finish_step(p, phase, record_every, red);
+    finish_step(p, phase, record_every, fused != 0, red);
 }
 
 // Observables of the current state: K and P from the velocities, U and W
@@ -177,36 +184,37 @@ __global__ __launch_bounds__(kIntThreads) void k_observe(KParams p)
 }
 
 template <class B>
-static void integrate_pass(const B& b, const LaunchShape& sh, int phase, int record_every,
-                           hipStream_t s, bool bin = false)
+static void integrate_pass(const B& b, const LaunchShape& sh, int phase, hipStream_t s, bool bin,
+                           bool to_scratch)
 {
     const dim3 g(sh.grid[G_INTEGRATE]), t(kIntThreads);
+    const int out = to_scratch ? 1 : 0;
     if (bin && phase <= 1) {
         if (sh.precision == MD_FP64)
-            hipLaunchKernelGGL((k_integrate<double, B, true>), g, t, 0, s, b, phase, record_every);
+            hipLaunchKernelGGL((k_integrate<double, B, true>), g, t, 0, s, b, phase, out);
         else
-            hipLaunchKernelGGL((k_integrate<float, B, true>), g, t, 0, s, b, phase, record_every);
+            hipLaunchKernelGGL((k_integrate<float, B, true>), g, t, 0, s, b, phase, out);
     } else if (sh.precision == MD_FP64) {
-        hipLaunchKernelGGL((k_integrate<double, B, false>), g, t, 0, s, b, phase, record_every);
+        hipLaunchKernelGGL((k_integrate<double, B, false>), g, t, 0, s, b, phase, out);
     } else {
-        hipLaunchKernelGGL((k_integrate<float, B, false>), g, t, 0, s, b, phase, record_every);
+        hipLaunchKernelGGL((k_integrate<float, B, false>), g, t, 0, s, b, phase, out);
     }
 }
 
 template <class B>
 static void integrate_finish(const B& b, const LaunchShape& sh, int phase, int record_every,
-                             hipStream_t s)
+                             hipStream_t s, bool fused)
 {
     hipLaunchKernelGGL(k_int_finish<B>, dim3(sh.grid[G_ONE]), dim3(kFinishThreads), 0, s, b,
-                       phase, record_every);
+                       phase, record_every, fused ? 1 : 0);
 }
 
 template <class B>
 static void integrate_seq(const B& b, const LaunchShape& sh, int phase, int record_every,
                           hipStream_t s)
 {
-    integrate_pass(b, sh, phase, record_every, s);
-    integrate_finish(b, sh, phase, record_every, s);
+    integrate_pass(b, sh, phase, s, false, false);
+    integrate_finish(b, sh, phase, record_every, s, false);
 }
 
 void launch_integrate(const KParams& p, int phase, int record_every, hipStream_t s)
@@ -214,21 +222,33 @@ void launch_integrate(const KParams& p, int phase, int record_every, hipStream_t
     integrate_seq(Single{p}, shape_of(p), phase, record_every, s);
 }
 
-void launch_integrate_pass(const KParams& p, int phase, int record_every, hipStream_t s,
-                           bool bin)
+void launch_integrate_pass(const KParams& p, int phase, hipStream_t s, bool bin, bool to_scratch)
 {
-    integrate_pass(Single{p}, shape_of(p), phase, record_every, s, bin);
+    integrate_pass(Single{p}, shape_of(p), phase, s, bin, to_scratch);
 }
 
-void launch_integrate_finish(const KParams& p, int phase, int record_every, hipStream_t s)
+void launch_integrate_finish(const KParams& p, int phase, int record_every, hipStream_t s,
+                             bool fused)
 {
-    integrate_finish(Single{p}, shape_of(p), phase, record_every, s);
+    integrate_finish(Single{p}, shape_of(p), phase, record_every, s, fused);
 }
 
 void launch_integrate(const Batch& b, const LaunchShape& sh, int phase, int record_every,
                       hipStream_t s)
 {
     integrate_seq(b, sh, phase, record_every, s);
+}
+
+void launch_integrate_pass(const Batch& b, const LaunchShape& sh, int phase, hipStream_t s,
+                           bool to_scratch)
+{
+    integrate_pass(b, sh, phase, s, false, to_scratch);
+}
+
+void launch_integrate_finish(const Batch& b, const LaunchShape& sh, int phase, int record_every,
+                             hipStream_t s, bool fused)
+{
+    integrate_finish(b, sh, phase, record_every, s, fused);
 }
 
 void launch_observe(const KParams& p, hipStream_t s)

@@ -31,9 +31,16 @@ struct DevState {
     int32_t  flags;        // MD_FLAG_* latched bits
     int32_t  max_occ;      // largest cell occupancy at the last build
     int32_t  max_nl;       // longest list at the last build
-    int32_t  pad[3];
+    int32_t  record;       // 1: the history asks for the step the next fused force pass ends
+    int32_t  pad[2];
     double   obs[8];       // U, K, W, Px, Py, Pz, dmax2, spare (md_reduce)
+    // largest squared displacement of the drift in a fused force pass, as the
+    // bits of a non-negative double: workgroup w folds its own into slot
+    // w mod kDmaxSlots by an atomic maximum; the finish reads and clears them
+    unsigned long long dmax_slot[16];
 };
+constexpr int kDmaxSlots = 16;
+static_assert(sizeof(DevState) <= 256, "the control block fills its workspace region");
 
 // Everything a kernel needs.
 struct KParams {
@@ -201,6 +208,21 @@ __device__ __forceinline__ KParams global_view(const KParams& q)
     return p;
 }
 
+// The state's positions and the scratch positions exchanged (see
+// launch_forces_step).
+__host__ __device__ inline void flip_positions(KParams& p)
+{
+    double* t = p.x;
+    p.x = p.sx;
+    p.sx = t;
+    t = p.y;
+    p.y = p.sy;
+    p.sy = t;
+    t = p.z;
+    p.z = p.sz;
+    p.sz = t;
+}
+
 // A single system: the parameters are the kernel argument.
 struct Single {
     KParams p;
@@ -238,6 +260,7 @@ struct Batch {
     const uint16_t* __restrict__ rep_of;
     int32_t rep_base[G_KINDS];
     int32_t R;
+    int32_t flip = 0;  // the positions are in the scratch arrays, and the other way round
     __device__ __forceinline__ bool fetch(GridKind k, Wg& w, KParams& out) const
     {
         const int blk = (int)blockIdx.x;
@@ -261,6 +284,7 @@ struct Batch {
         w.n = count[(int)k * R + r];
         if (w.id >= w.n) return false;
         out = global_view(kp[r]);
+        if (flip) flip_positions(out);
         return true;
     }
 };
@@ -323,7 +347,9 @@ void launch_clear(const KParams& p, hipStream_t s);
 // gated by the rebuild flag); kFoldCopy (tiled pipeline with reorder, list
 // mode) leaves the cell-sorted data in the scratch arrays, and the list
 // build copies each tile's home atoms into the state arrays (saving the
-// separate copy-back pass and its launch).
+// separate copy-back pass and its launch).  The forces are left out of that
+// permutation: the force pass that follows in every such sequence writes them
+// anew.
 constexpr int kFoldCopy = 2;
 // Further launch_cells flags of md_step's cells-only sequence: kFoldBin --
 // the integration pass has already binned the atoms (k_bin is left out);
@@ -353,9 +379,32 @@ void launch_integrate(const KParams& p, int phase, int record_every, hipStream_t
 // The two halves of launch_integrate: the per-atom pass, then the per-system
 // finish (reductions, step count and record, rebuild decision).
 // bin: the pass also bins the atoms (cells-only steps; with phase <= 1 only).
-void launch_integrate_pass(const KParams& p, int phase, int record_every, hipStream_t s,
-                           bool bin = false);
-void launch_integrate_finish(const KParams& p, int phase, int record_every, hipStream_t s);
+// to_scratch: the drifted positions go to the scratch arrays.
+void launch_integrate_pass(const KParams& p, int phase, hipStream_t s, bool bin = false,
+                           bool to_scratch = false);
+// fused: the pass was a fused force pass (its partials, see launch_forces_step)
+void launch_integrate_finish(const KParams& p, int phase, int record_every, hipStream_t s,
+                             bool fused = false);
+// The force pass of a step with the integration pass that follows it (phase
+// 1): each home atom's force is used where it is summed, so neither the
+// forces nor the old positions pass through memory.  The drifted positions go
+// to the scratch arrays, since other tiles still read the old ones: the next
+// kernels take flip_positions of p.  Tiled lists with reorder (which have the
+// scratch arrays), no third law, no bonded terms; fused_fits: its partials of a
+// recorded step (K, P per tile, behind the tiles' U, W) fit the partials'
+// region.
+inline bool fused_fits(const KParams& p)
+{
+    return p.pipeline == MD_PIPE_TILED && p.mode == MD_NEIGHBOR_LIST && p.reorder &&
+           !p.newton3 && !p.bonded_on &&
+           6ll * p.n_tiles <= 2ll * max_force_blocks(p.n, p.ncell);
+}
+void launch_forces_step(const KParams& p, hipStream_t s);
+void launch_forces_step(const Batch& b, const LaunchShape& sh, hipStream_t s);
+void launch_integrate_pass(const Batch& b, const LaunchShape& sh, int phase, hipStream_t s,
+                           bool to_scratch);
+void launch_integrate_finish(const Batch& b, const LaunchShape& sh, int phase, int record_every,
+                             hipStream_t s, bool fused);
 void launch_observe(const KParams& p, hipStream_t s);
 
 }  // namespace md
