@@ -254,12 +254,23 @@ extern "C" md_status md_init(const md_params* in, md_ctx** out)
     b[R_SX] = b[R_SY] = b[R_SZ] = b[R_SVX] = b[R_SVY] = b[R_SVZ] = perm * sizeof(double) * n;
     b[R_SFX] = b[R_SFY] = b[R_SFZ] = perm * fsz * n;
     b[R_SID] = b[R_SCELL] = perm * sizeof(int32_t) * n;
+    const bool cells2 = !nl && !perm && p.pipeline == MD_PIPE_TILED;
     b[R_APART] = ap_split > 1 ? fsz * 3 * (size_t)ap_split * npad : 0;
     const int64_t fblocks = max_force_blocks(n, ncell);
     b[R_FPART] = sizeof(double) * 2 * (size_t)(ap_blocks > fblocks ? ap_blocks : fblocks);
     b[R_IPART] = sizeof(double) * 8 * kIntegrateGridMax;
     b[R_HIST] = sizeof(md_record) * kHistCap;
     relayout(c);
+    if (cells2) {
+        // second positions for the fused steps of a cells-only system without
+        // reorder, unless they would push the workspace past the static array
+        const size_t more = 3 * align_up(sizeof(double) * (size_t)n);
+        if (c->ws_bytes > MD_STATIC_WORKSPACE_BYTES ||
+            c->ws_bytes + more <= MD_STATIC_WORKSPACE_BYTES) {
+            b[R_SX] = b[R_SY] = b[R_SZ] = sizeof(double) * n;
+            relayout(c);
+        }
+    }
 
     KParams& k = c->kp;
     memset(&k, 0, sizeof(k));
@@ -718,12 +729,10 @@ static md_status step_launches(md_ctx* c, hipStream_t s, bool first, int32_t n,
     const bool cells = tiled && !nl;
     const int cflags = fold | (cells ? kFoldBin | kSortSmallOk : 0);
     const int fflags = cells ? fold : 0;
-    // a small cells-only system finishes the integration pass inside its one
-    // cell-sort workgroup (one launch less)
-    const bool small = cells && k.n <= kSortSmall && !k.bonded_on;
+    // the finish with the cell build behind it (one launch for a small system)
     auto finish_and_cells = [&](int phase) {
-        if (small) {
-            launch_sort_small_finish(k, phase, record_every, s);
+        if (tiled && !k.bonded_on) {
+            launch_finish_cells(k, cflags, phase, record_every, false, s);
         } else {
             launch_integrate_finish(k, phase, record_every, s);
             cells_any(k, cflags, s);
@@ -744,7 +753,10 @@ static md_status step_launches(md_ctx* c, hipStream_t s, bool first, int32_t n,
         timed(c, MD_PART_INTEGRATE,
               [&] { launch_integrate_pass(k, phase, s, cells); });
         const bool reorder = layer_reorder_on(c) && (step0 + i + 1) % k.reorder == 0;
-        if (small) {  // the finish and the cell build in one launch (counted as cells)
+        if (!c->timing && !reorder) {
+            finish_and_cells(phase);
+        } else if (cells && k.n <= kSortSmall && !k.bonded_on) {
+            // the finish and the cell build in one launch (counted as cells)
             timed(c, MD_PART_CELLS, [&] { finish_and_cells(phase); });
         } else {
             timed(c, MD_PART_ENERGY, [&] { launch_integrate_finish(k, phase, record_every, s); });
@@ -765,6 +777,7 @@ static md_status step_launches(md_ctx* c, hipStream_t s, bool first, int32_t n,
 // (launch_forces_step): an integration pass starts the first step, every body
 // ends one step and starts the next (cells and list if needed, the fused force
 // pass, its finish), and a force pass and an integration pass end the last.
+// A finish is launched with the cell build behind it.
 // The positions change places with the scratch arrays in every body: `flip`
 // says where they are, and the first pass puts them where the last body will
 // leave them in the state arrays.
@@ -777,16 +790,24 @@ static KParams flipped(const KParams& k, bool flip)
     return q;
 }
 
+// Cells (after the finish of a pass), list and force pass flags of a fused body.
+static int fused_cells_flags(const KParams& k)
+{
+    return (k.reorder ? kFoldCopy : 0) |
+           (k.mode == MD_CELLS_ONLY ? kFoldBin | kSortSmallOk : 0);
+}
+
 static void fused_bodies(const md_ctx* c, hipStream_t s, int32_t n, int32_t record_every,
                          bool& flip)
 {
+    const int flags = fused_cells_flags(c->kp);
+    const bool flips = fused_flips(c->kp);
     for (int32_t i = 0; i < n; ++i) {
         const KParams q = flipped(c->kp, flip);
-        launch_cells(q, kFoldCopy, s);
-        launch_neighbors(q, kFoldCopy, s);
+        if (q.mode == MD_NEIGHBOR_LIST) launch_neighbors(q, kFoldCopy, s);
         launch_forces_step(q, s);
-        launch_integrate_finish(q, 1, record_every, s, true);
-        flip = !flip;
+        if (flips) flip = !flip;
+        launch_finish_cells(flipped(c->kp, flip), flags, 1, record_every, true, s);
     }
 }
 
@@ -842,7 +863,7 @@ static md_status step_graphs(md_ctx* c, int32_t len, int32_t n_graphs, int32_t r
         if (hipGraphLaunch(c->gexec, run) != hipSuccess) return MD_ERR_HIP;
     // several replays are of kGraphSteps (even) bodies each: the places are the
     // same before and after
-    if (fused && len % 2 != 0) flip = !flip;
+    if (fused && len % 2 != 0 && fused_flips(c->kp)) flip = !flip;
     if (own && (hipEventRecord(c->gev[1], run) != hipSuccess ||
                 hipStreamWaitEvent(c->stream, c->gev[1], 0) != hipSuccess))
         return MD_ERR_HIP;
@@ -862,9 +883,11 @@ extern "C" md_status md_step(md_ctx* c, int32_t n_steps, int32_t record_every)
         const KParams& k = c->kp;
         hipStream_t s = c->stream;
         const int32_t rest = n_steps - 1;
-        flip = rest % 2 != 0;
-        launch_integrate_pass(k, 0, s, false, flip);
-        launch_integrate_finish(k, 0, record_every, s);
+        const bool nl = k.mode == MD_NEIGHBOR_LIST;
+        const int flags = fused_cells_flags(k);
+        flip = fused_flips(k) && rest % 2 != 0;
+        launch_integrate_pass(k, 0, s, !nl, flip);
+        launch_finish_cells(flipped(k, flip), flags, 0, record_every, false, s);
         st = MD_OK;
         if (!c->graph_on || n_steps <= kGraphMin) {
             fused_bodies(c, s, rest, record_every, flip);
@@ -874,9 +897,8 @@ extern "C" md_status md_step(md_ctx* c, int32_t n_steps, int32_t record_every)
             if (st == MD_OK) fused_bodies(c, s, rest - n_graphs * len, record_every, flip);
         }
         if (st == MD_OK) {
-            launch_cells(k, kFoldCopy, s);
-            launch_neighbors(k, kFoldCopy, s);
-            launch_forces(k, s);
+            if (nl) launch_neighbors(k, kFoldCopy, s);
+            launch_forces(k, s, nl ? 0 : flags & kFoldCopy);
         }
     } else if (c->timing || !c->graph_on || layer_reorder_on(c) || n_steps <= kGraphMin) {
         st = step_launches(c, c->stream, true, n_steps, record_every, step0);
@@ -1161,8 +1183,8 @@ extern "C" md_status md_traj_backward(md_ctx* c, const md_traj_params* tp, void*
         if ((st = checkpoint(c, ck, false)) != MD_OK) return st;
         rebuild_all(c);
         for (int j = 1; j < s1 - s0; ++j) {
-            launch_integrate(k, j == 1 ? 0 : 1, 0, sm);
-            launch_cells(k, 0, sm);
+            launch_integrate_pass(k, j == 1 ? 0 : 1, sm);
+            launch_finish_cells(k, 0, j == 1 ? 0 : 1, 0, false, sm);
             launch_neighbors(k, 0, sm);
             launch_forces(k, sm);
             for (int d = 0; d < 3; ++d)

@@ -171,7 +171,7 @@ md_status upload(md_batch* b)
 void step_sequence(md_batch* b, int32_t n_steps, int32_t record_every)
 {
     const bool nl = b->sh.mode == MD_NEIGHBOR_LIST;
-    bool fused = true;
+    bool fused = nl;
     for (const md_ctx* c : b->rep) fused = fused && fused_fits(c->kp);
     if (fused) {  // the integration in the force pass, as md_step
         const int32_t rest = n_steps - 1;

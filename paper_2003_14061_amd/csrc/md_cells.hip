@@ -242,14 +242,14 @@ __global__ void k_cellsort(B b, int force)
 // (finish_step), in place of k_int_finish.
 template <typename F, class B, Permute kPermute, bool kFinish>
 __global__ __launch_bounds__(kScanThreads) void k_sort_small(B b, int force, int phase,
-                                                             int record_every)
+                                                             int record_every, int fused)
 {
     Wg wg;
     KParams p;
     if (!b.fetch(G_ONE, wg, p)) return;
     if (kFinish) {
         __shared__ double red[(kScanThreads / kWave) * 5];
-        finish_step(p, phase, record_every, false, red);
+        finish_step(p, phase, record_every, fused != 0, red);
         __syncthreads();
     } else if (!rebuild_on(p, force)) {
         return;
@@ -262,64 +262,226 @@ __global__ __launch_bounds__(kScanThreads) void k_sort_small(B b, int force, int
     for (int q = threadIdx.x; q < p.n; q += blockDim.x) sort_slot<F, kPermute>(p, q);
 }
 
-// k_sort_small's cells-only form (kFinish) with its tables in LDS: the cell
-// starts (ncell + 1), and per slot-order position q the atom with its cell
-// (atom | cell << kSortAtomBits) and its id (2 n), so that the scatter and the
-// in-cell sort read global memory only for the binning of the integration
-// pass and the atom data they permute.  Same results as k_sort_small; for
-// systems whose tables fit (sort_lds_bytes).
+// The whole cell build of a small system by one workgroup, its tables in LDS:
+// the cell starts (ncell + 1), and per slot-order position q the atom with its
+// cell (atom | cell << kSortAtomBits) and its id (2 n), so that global memory is
+// read only for the atoms' positions (or the binning of the integration pass,
+// in cells-only steps) and ids and the data that are permuted.  One launch in
+// place of five (the finish, k_bin, k_scan, k_scatter, k_cellsort): a step that
+// does not rebuild pays for one idle workgroup, and a rebuild is one chain of
+// barriers.  Bound by that workgroup's round trips to memory, so the loads of
+// four atoms per thread are issued together.  Same results as the separate
+// kernels.  List steps of 500 WCA atoms 32 -> 15.6 us, of 10 007 LJ atoms
+// 28.7 -> 23.8 us (a rebuild of the latter takes 41 us here, 27 us over the
+// whole chip, but an idle step 2.2 us in place of five launches).
 constexpr int kSortAtomBits = 14;  // atoms of a small system: at most kSortSmall = 2^14
 
-template <bool kPermute>
-__global__ __launch_bounds__(kScanThreads) void k_sort_lds(Single b, int phase, int record_every)
+struct SmallCells {
+    int finish;        // 0 none; 1 / 2: first finish the integration pass / the fused force pass
+    int phase, record_every;
+    int force;         // build whatever the rebuild flag says
+};
+
+// kBin: bin the atoms here (else the integration pass has).
+template <bool kPermute, bool kBin>
+__global__ __launch_bounds__(kScanThreads) void k_cells_lds(Single b, SmallCells a)
 {
     const KParams& p = b.p;
-    {
-        __shared__ double red[(kScanThreads / kWave) * 5];
-        finish_step(p, phase, record_every, false, red);
-        __syncthreads();
+    constexpr int T = kScanThreads, U = 4;
+    if (a.finish) {
+        __shared__ double red[(T / kWave) * 5];
+        if (!finish_step(p, a.phase, a.record_every, a.finish == 2, red) && !a.force) return;
+    } else if (!rebuild_on(p, a.force)) {
+        return;
     }
     extern __shared__ int lds[];
     int* cs = lds;                      // [ncell + 1]
     int* slot_ac = cs + p.ncell + 1;    // [n] atom | cell << kSortAtomBits
     int* slot_id = slot_ac + p.n;       // [n]
-    __shared__ int wsum[kScanThreads / kWave];
-    scan_cells(p, wsum, cs);
-    __syncthreads();
-    for (int i = threadIdx.x; i < p.n; i += blockDim.x) {
-        const int c = p.cell_of[i], sl = p.slot[i], key = p.id[i];
-        const int q = cs[c] + sl;
-        slot_ac[q] = i | (c << kSortAtomBits);
-        slot_id[q] = key;
+    __shared__ int wsum[T / kWave];
+    const int tid = threadIdx.x;
+    if (kBin) {
+        // fold, cell and arrival rank (see k_bin), the rank by LDS atomics: kept
+        // as cell | rank in slot_ac and slot_id of the atom's own index until the
+        // cell starts are known
+        for (int c = tid; c <= p.ncell; c += T) cs[c] = 0;
+        __syncthreads();
+        for (int i0 = tid; i0 < p.n; i0 += U * T) {
+            double x[U], y[U], z[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * T;
+                if (i < p.n) {
+                    x[u] = p.x[i];
+                    y[u] = p.y[i];
+                    z[u] = p.z[i];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * T;
+                if (i < p.n) {
+                    x[u] = wrap(x[u], p.L);
+                    y[u] = wrap(y[u], p.L);
+                    z[u] = wrap(z[u], p.L);
+                    p.x[i] = x[u];
+                    p.y[i] = y[u];
+                    p.z[i] = z[u];
+                    const int c = cell_of_pos(x[u], y[u], z[u], p);
+                    p.cell_of[i] = c;
+                    slot_ac[i] = c;
+                    slot_id[i] = atomicAdd(&cs[c], 1);
+                }
+            }
+        }
+        __syncthreads();
+        // exclusive scan of the counts in place, four cells per thread at a time
+        int carry = 0, m = 0;
+        for (int c0 = 0; c0 < p.ncell; c0 += T * kScanPer) {
+            const int c = c0 + tid * kScanPer;
+            int v[kScanPer], sum = 0;
+#pragma unroll
+            for (int k = 0; k < kScanPer; ++k) {
+                v[k] = c + k < p.ncell ? cs[c + k] : 0;
+                sum += v[k];
+                m = v[k] > m ? v[k] : m;
+            }
+            int total;
+            int ex = carry + workgroup_scan_excl(sum, wsum, total);
+#pragma unroll
+            for (int k = 0; k < kScanPer; ++k) {
+                if (c + k < p.ncell) {
+                    cs[c + k] = ex;
+                    p.cell_start[c + k] = ex;
+                }
+                ex += v[k];
+            }
+            carry += total;
+        }
+        const int occ = workgroup_max(m);
+        if (tid == 0) {
+            cs[p.ncell] = carry;
+            p.cell_start[p.ncell] = carry;
+            p.dev->max_occ = occ;
+            p.dev->max_nl = 0;
+        }
+        __syncthreads();
+        // every atom to its slot: read all of a thread's entries before any is
+        // overwritten
+        constexpr int kPer = kSortSmall / T;
+        int q[kPer], cc[kPer], key[kPer];
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int i = tid + u * T;
+            if (i < p.n) {
+                cc[u] = slot_ac[i];
+                q[u] = cs[cc[u]] + slot_id[i];
+                key[u] = p.id[i];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int i = tid + u * T;
+            if (i < p.n) {
+                slot_ac[q[u]] = i | (cc[u] << kSortAtomBits);
+                slot_id[q[u]] = key[u];
+            }
+        }
+    } else {
+        scan_cells(p, wsum, cs);
+        __syncthreads();
+        for (int i0 = tid; i0 < p.n; i0 += U * T) {
+            int c[U], sl[U], key[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * T;
+                if (i < p.n) {
+                    c[u] = p.cell_of[i];
+                    sl[u] = p.slot[i];
+                    key[u] = p.id[i];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * T;
+                if (i < p.n) {
+                    const int q = cs[c[u]] + sl[u];
+                    slot_ac[q] = i | (c[u] << kSortAtomBits);
+                    slot_id[q] = key[u];
+                }
+            }
+        }
     }
     __syncthreads();
-    for (int q = threadIdx.x; q < p.n; q += blockDim.x) {
-        const int ac = slot_ac[q], s = ac & ((1 << kSortAtomBits) - 1), c = ac >> kSortAtomBits;
-        const int a = cs[c], cnt = cs[c + 1] - a, key = slot_id[q];
-        int rank = 0;
-        for (int j = 0; j < cnt; ++j) rank += slot_id[a + j] < key ? 1 : 0;
-        const int d = a + rank;
-        p.order[d] = s;
-        if (kPermute) {
-            p.sx[d] = p.x[s];
-            p.sy[d] = p.y[s];
-            p.sz[d] = p.z[s];
-            p.svx[d] = p.vx[s];
-            p.svy[d] = p.vy[s];
-            p.svz[d] = p.vz[s];
-            p.sid[d] = key;
-            p.scell[d] = c;
+    for (int q0 = tid; q0 < p.n; q0 += U * T) {
+        int d[U], src[U], key[U], cell[U];
+        double v[U][6];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int q = q0 + u * T;
+            if (q < p.n) {
+                const int ac = slot_ac[q];
+                src[u] = ac & ((1 << kSortAtomBits) - 1);
+                cell[u] = ac >> kSortAtomBits;
+                if (kPermute) {
+                    v[u][0] = p.x[src[u]];
+                    v[u][1] = p.y[src[u]];
+                    v[u][2] = p.z[src[u]];
+                    v[u][3] = p.vx[src[u]];
+                    v[u][4] = p.vy[src[u]];
+                    v[u][5] = p.vz[src[u]];
+                }
+                const int first = cs[cell[u]], cnt = cs[cell[u] + 1] - first;
+                key[u] = slot_id[q];
+                int rank = 0;
+                for (int j = 0; j < cnt; ++j) rank += slot_id[first + j] < key[u] ? 1 : 0;
+                d[u] = first + rank;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (q0 + u * T < p.n) {
+                p.order[d[u]] = src[u];
+                if (kPermute) {
+                    p.sx[d[u]] = v[u][0];
+                    p.sy[d[u]] = v[u][1];
+                    p.sz[d[u]] = v[u][2];
+                    p.svx[d[u]] = v[u][3];
+                    p.svy[d[u]] = v[u][4];
+                    p.svz[d[u]] = v[u][5];
+                    p.sid[d[u]] = key[u];
+                    p.scell[d[u]] = cell[u];
+                }
+            }
         }
     }
 }
 
-// LDS bytes of k_sort_lds for p, or 0 when its tables do not fit (60 KiB) or
-// a cell index does not fit beside the atom.
-static size_t sort_lds_bytes(const KParams& p)
+// LDS bytes of k_cells_lds for p, or 0 when the system is not small, a cell
+// index does not fit beside the atom, or its tables do not fit (144 KiB of the
+// CU's 160).
+static size_t cells_lds_bytes(const KParams& p)
 {
-    if (p.n > (1 << kSortAtomBits) || p.ncell >= (1 << (31 - kSortAtomBits))) return 0;
+    if (p.pipeline != MD_PIPE_TILED || p.n > kSortSmall || p.ncell >= (1 << (31 - kSortAtomBits)))
+        return 0;
     const size_t b = sizeof(int) * ((size_t)p.ncell + 1 + 2 * (size_t)p.n);
-    return b <= 61440 ? b : 0;
+    return b <= 144 * 1024 ? b : 0;
+}
+
+static void cells_lds(const KParams& p, const SmallCells& a, bool bin, hipStream_t s)
+{
+    const dim3 one(1), t(kScanThreads);
+    const size_t lds = cells_lds_bytes(p);
+    const Single b{p};
+    if (p.reorder && bin)
+        hipLaunchKernelGGL((k_cells_lds<true, true>), one, t, lds, s, b, a);
+    else if (p.reorder)
+        hipLaunchKernelGGL((k_cells_lds<true, false>), one, t, lds, s, b, a);
+    else if (bin)
+        hipLaunchKernelGGL((k_cells_lds<false, true>), one, t, lds, s, b, a);
+    else
+        hipLaunchKernelGGL((k_cells_lds<false, false>), one, t, lds, s, b, a);
 }
 
 template <typename F, class B>
@@ -361,16 +523,16 @@ static void cells_seq(const B& b, const LaunchShape& sh, int flags, hipStream_t 
         const dim3 one(1), t(kScanThreads);
         if (!sh.reorder)
             hipLaunchKernelGGL((k_sort_small<double, B, P_NONE, false>), one, t, 0, s, b, force,
-                               0, 0);
+                               0, 0, 0);
         else if (!copy)
             hipLaunchKernelGGL((k_sort_small<double, B, P_STATE, false>), one, t, 0, s, b, force,
-                               0, 0);
+                               0, 0, 0);
         else if (sh.precision == MD_FP64)
             hipLaunchKernelGGL((k_sort_small<double, B, P_ALL, false>), one, t, 0, s, b, force, 0,
-                               0);
+                               0, 0);
         else
             hipLaunchKernelGGL((k_sort_small<float, B, P_ALL, false>), one, t, 0, s, b, force, 0,
-                               0);
+                               0, 0);
     } else {
         hipLaunchKernelGGL(k_scan<B>, dim3(sh.grid[G_ONE]), dim3(kScanThreads), 0, s, b, force);
         hipLaunchKernelGGL(k_scatter<B>, atoms, blk, 0, s, b, force);
@@ -393,10 +555,15 @@ static void cells_seq(const B& b, const LaunchShape& sh, int flags, hipStream_t 
 
 void launch_clear(const KParams& p, hipStream_t s) { clear_seq(Single{p}, shape_of(p), s); }
 
-void launch_cells(const KParams& p, int force, hipStream_t s)
+void launch_cells(const KParams& p, int flags, hipStream_t s)
 {
-    const bool small = (force & kSortSmallOk) && p.n <= kSortSmall;
-    cells_seq(Single{p}, shape_of(p), force, s, small ? p.n : 0);
+    // (with reorder, k_cells_lds leaves the copy-back to a later pass)
+    if (cells_lds_bytes(p) && (!p.reorder || (flags & kFoldCopy))) {
+        cells_lds(p, SmallCells{0, 0, 0, flags & 1}, !(flags & kFoldBin), s);
+        return;
+    }
+    const bool small = (flags & kSortSmallOk) && p.n <= kSortSmall;
+    cells_seq(Single{p}, shape_of(p), flags, s, small ? p.n : 0);
 }
 
 // The cell offsets from the occupancy counts alone (forced), for the layer
@@ -406,25 +573,27 @@ void launch_cell_scan(const KParams& p, hipStream_t s)
     hipLaunchKernelGGL(k_scan<Single>, dim3(1), dim3(kScanThreads), 0, s, Single{p}, 1);
 }
 
-// The cells-only step's cell build of a small system (atoms binned by the
-// integration pass) with the finish of that pass in front (see k_sort_small).
-void launch_sort_small_finish(const KParams& p, int phase, int record_every, hipStream_t s)
+void launch_finish_cells(const KParams& p, int flags, int phase, int record_every, bool fused,
+                         hipStream_t s)
 {
-    const dim3 one(1), t(kScanThreads);
-    const Single b{p};
-    const size_t lds = sort_lds_bytes(p);
-    if (lds) {
-        if (p.reorder)
-            hipLaunchKernelGGL(k_sort_lds<true>, one, t, lds, s, b, phase, record_every);
-        else
-            hipLaunchKernelGGL(k_sort_lds<false>, one, t, lds, s, b, phase, record_every);
-    } else if (p.reorder) {
-        hipLaunchKernelGGL((k_sort_small<double, Single, P_STATE, true>), one, t, 0, s, b, 1,
-                           phase, record_every);
-    } else {
-        hipLaunchKernelGGL((k_sort_small<double, Single, P_NONE, true>), one, t, 0, s, b, 1,
-                           phase, record_every);
+    if (cells_lds_bytes(p) && (!p.reorder || (flags & kFoldCopy))) {
+        cells_lds(p, SmallCells{fused ? 2 : 1, phase, record_every, flags & 1},
+                  !(flags & kFoldBin), s);
+        return;
     }
+    if ((flags & kFoldBin) && (flags & kSortSmallOk) && p.n <= kSortSmall) {
+        const dim3 one(1), t(kScanThreads);
+        const Single b{p};
+        if (p.reorder)
+            hipLaunchKernelGGL((k_sort_small<double, Single, P_STATE, true>), one, t, 0, s, b, 1,
+                               phase, record_every, fused ? 1 : 0);
+        else
+            hipLaunchKernelGGL((k_sort_small<double, Single, P_NONE, true>), one, t, 0, s, b, 1,
+                               phase, record_every, fused ? 1 : 0);
+        return;
+    }
+    launch_integrate_finish(p, phase, record_every, s, fused);
+    launch_cells(p, flags, s);
 }
 
 void launch_clear(const Batch& b, const LaunchShape& sh, hipStream_t s) { clear_seq(b, sh, s); }

@@ -198,6 +198,25 @@ __device__ __forceinline__ int wave_scan_incl(int v)
     return v;
 }
 
+// Exclusive prefix sum of v over the workgroup and the total (in every
+// thread); wsum: LDS, one int per wave.
+__device__ __forceinline__ int workgroup_scan_excl(int v, int* wsum, int& total)
+{
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    const int nw = blockDim.x / kWave;
+    const int inc = wave_scan_incl(v);
+    if (lane == kWave - 1) wsum[wid] = inc;
+    __syncthreads();
+    int before = 0;
+    total = 0;
+    for (int w = 0; w < nw; ++w) {
+        before += w < wid ? wsum[w] : 0;
+        total += wsum[w];
+    }
+    __syncthreads();
+    return before + inc - v;
+}
+
 // The maximum of v over the workgroup, valid in thread 0 (0 elsewhere).  Every
 // thread of the workgroup calls it.  Kernels fold a per-thread maximum into a
 // device-wide one with this and a single global atomic per workgroup: atomics

@@ -57,8 +57,7 @@ __device__ __forceinline__ bool recorded(int64_t step, int record_every)
 
 // Finish a completed step: count it, and on steps the history asks for, sum
 // U, W (last force pass) and K, P (the partials of the integration pass, or
-// with fused those of the fused force pass: component c of tile t at
-// fpart[(2 + c) n_tiles + t]) and append them.
+// with fused those of the fused force pass, step_part) and append them.
 __device__ __forceinline__ void record_step(const KParams& p, int n_wg, int record_every,
                                             bool fused, double* red)
 {
@@ -75,8 +74,8 @@ __device__ __forceinline__ void record_step(const KParams& p, int n_wg, int reco
     }
     double kp[4];
     for (int c = 0; c < 4; ++c)
-        kp[c] = fused ? finish_sum<kFinishThreads>(p.fpart + (2 + c) * (int64_t)p.n_tiles,
-                                                   p.n_tiles, 1, 0, red)
+        kp[c] = fused ? finish_sum<kFinishThreads>(step_part(p) + c * (int64_t)p.nblk_force,
+                                                   p.nblk_force, 1, 0, red)
                       : finish_sum<kFinishThreads>(p.ipart, n_wg, 8, c, red);
     if (threadIdx.x == 0) {
         md_record* r = p.hist + (dd->hist_count % kHistCap);
@@ -96,12 +95,13 @@ __device__ __forceinline__ void record_step(const KParams& p, int n_wg, int reco
 
 // The end of an integration pass: count the step and record it (phase >= 1),
 // and from the largest displacement decide whether the cells and list are
-// rebuilt before the next force pass (phase <= 1).  By one workgroup of at
+// rebuilt before the next force pass (phase <= 1; returned in every thread).  By one workgroup of at
 // least kFinishThreads threads (red: LDS, (blockDim / 64) * 5 doubles).  fused:
 // the pass was a fused force pass (launch_forces_step).
-__device__ __forceinline__ void finish_step(const KParams& p, int phase, int record_every,
+__device__ __forceinline__ bool finish_step(const KParams& p, int phase, int record_every,
                                             bool fused, double* red)
 {
+    bool rebuild = false;
     const int n_wg = grid_of(p, G_INTEGRATE);
     if (phase >= 1) record_step(p, n_wg, record_every, fused, red);
     if (phase <= 1) {
@@ -130,13 +130,15 @@ __device__ __forceinline__ void finish_step(const KParams& p, int phase, int rec
             if (rb) d->n_rebuilds += 1;
             rb_all = rb;
         }
+        __syncthreads();
+        rebuild = rb_all != 0;
         if (p.gate_tab[0]) {  // a batch replica: its gate bits in the workgroup table
-            __syncthreads();
-            const uint16_t v = (uint16_t)(p.rep | (rb_all ? kGateBit : 0));
+            const uint16_t v = (uint16_t)(p.rep | (rebuild ? kGateBit : 0));
             for (int j = 0; j < 3; ++j)
                 for (int i = threadIdx.x; i < p.gate_n[j]; i += blockDim.x) p.gate_tab[j][i] = v;
         }
     }
+    return rebuild;
 }
 
 }  // namespace md

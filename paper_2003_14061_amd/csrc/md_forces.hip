@@ -30,6 +30,8 @@
 //
 // The energy and virial are reduced per workgroup (wave64 shuffles, then
 // LDS) and written as partials for the reduction kernels.
+#include <type_traits>
+
 #include "md_pair.h"
 #include "md_tiles.h"
 
@@ -416,7 +418,8 @@ __global__ __attribute__((amdgpu_waves_per_eu(6))) void k_forces_step(B b)
         if (threadIdx.x == 0) {
             p.fpart[2 * wg.id] = v[0];
             p.fpart[2 * wg.id + 1] = v[1];
-            for (int c = 0; c < 4; ++c) p.fpart[(2 + c) * (int64_t)p.n_tiles + wg.id] = v[2 + c];
+            double* const kp = step_part(p);
+            for (int c = 0; c < 4; ++c) kp[c * (int64_t)p.nblk_force + wg.id] = v[2 + c];
         }
     } else {
         HomeEnd<F, true, false> end;
@@ -454,10 +457,30 @@ __device__ __forceinline__ void walk_cell(const KParams& p, int i, double xi, do
     }
 }
 
+// The sums of this lane's atom i (valid where i < n), added across its group
+// of kCellLanes lanes, sub the lane's place in it.
+template <typename Acc>
+__device__ __forceinline__ void cells_sums(const KParams& p, const Wg& wg, Acc& a, int& i,
+                                           int& sub)
+{
+    const int64_t t = (int64_t)xcd_tile(wg.id, wg.n) * blockDim.x + threadIdx.x;
+    i = (int)(t / kCellLanes);
+    sub = (int)(t % kCellLanes);
+    if (i < p.n && sub < 27) {
+        const int c = p.cell_of[i], nc = p.nc;
+        const int cx = c % nc, cy = (c / nc) % nc, cz = c / (nc * nc);
+        const int dz = sub / 9 - 1, dy = (sub / 3) % 3 - 1, dx = sub % 3 - 1;
+        const int c2 = (wrap_cell(cz + dz, nc) * nc + wrap_cell(cy + dy, nc)) * nc +
+                       wrap_cell(cx + dx, nc);
+        walk_cell(p, i, p.x[i], p.y[i], p.z[i], c2, a);
+    }
+    group_sum<kCellLanes>(a);
+}
+
 // kCopy (md_step with reorder): the cell build left the sorted data in the
 // scratch arrays; the pass reads them there and each atom's lane 0 copies its
 // atom into the state arrays, forces written straight into the state.
-template <typename F, typename Acc, class B, bool kCopy>
+template <typename F, class B, bool kCopy>
 __global__ void k_forces_cells(B b)
 {
     Wg wg;
@@ -467,22 +490,9 @@ __global__ void k_forces_cells(B b)
     F* const fout[3] = {static_cast<F*>(pw.fx), static_cast<F*>(pw.fy),
                         static_cast<F*>(pw.fz)};
     __shared__ double red[(1024 / kWave) * 2];
-    const int64_t t = (int64_t)xcd_tile(wg.id, wg.n) * blockDim.x + threadIdx.x;
-    const int i = (int)(t / kCellLanes), sub = (int)(t % kCellLanes);
     LeanOf<F> a;
-    if (i < p.n && sub < 27) {
-        const int c = p.cell_of[i], nc = p.nc;
-        const int cx = c % nc, cy = (c / nc) % nc, cz = c / (nc * nc);
-        const int dz = sub / 9 - 1, dy = (sub / 3) % 3 - 1, dx = sub % 3 - 1;
-        const int c2 = (wrap_cell(cz + dz, nc) * nc + wrap_cell(cy + dy, nc)) * nc +
-                       wrap_cell(cx + dx, nc);
-        walk_cell(p, i, p.x[i], p.y[i], p.z[i], c2, a);
-    }
-    a.fx = lane_group_sum<kCellLanes>(a.fx);
-    a.fy = lane_group_sum<kCellLanes>(a.fy);
-    a.fz = lane_group_sum<kCellLanes>(a.fz);
-    a.q = lane_group_sum<kCellLanes>(a.q);
-    a.s6 = lane_group_sum<kCellLanes>(a.s6);
+    int i, sub;
+    cells_sums(p, wg, a, i, sub);
     double e[2] = {0.0, 0.0};
     if (i < p.n && sub == 0) {
         F fx, fy, fz;
@@ -499,6 +509,86 @@ __global__ void k_forces_cells(B b)
         p.fpart[2 * wg.id] = e[0];
         p.fpart[2 * wg.id + 1] = e[1];
     }
+}
+
+// The cells-only force pass with the integration pass that follows it (kick,
+// kick and drift, the new position folded and binned, as k_integrate with
+// kBin): see launch_forces_step.  The new positions go where no workgroup of
+// this launch reads: with kCopy the pass reads the sorted scratch arrays and
+// writes the state's, without it the scratch positions.  Energies and kinetic
+// sums of recorded steps only.  Bound by latency (one or two partners per lane):
+// 6.0 us at 4000 WCA atoms, against 6.3 + 6.5 us for the two passes; the step
+// 20.6 -> 13.6 us in two launches.
+template <typename F, bool kCopy, bool kEnergy>
+__device__ __forceinline__ void cells_step(const KParams& pw, const Wg& wg, double* red)
+{
+    const KParams p = kCopy ? scratch_view(pw) : pw;
+    using Sums = std::conditional_t<kEnergy, Lean<F>, LeanForce<F>>;
+    Sums a;
+    int i, sub;
+    cells_sums(p, wg, a, i, sub);
+    double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (i < p.n && sub == 0) {
+        double vx = p.vx[i], vy = p.vy[i], vz = p.vz[i];
+        double x = p.x[i], y = p.y[i], z = p.z[i];
+        F fx, fy, fz;
+        if constexpr (kEnergy) {
+            lean_finish(p, a, fx, fy, fz, v[0], v[1]);
+        } else {
+            const F k = (F)p.eps48;
+            fx = k * a.fx;
+            fy = k * a.fy;
+            fz = k * a.fz;
+        }
+        const double gx = (double)fx, gy = (double)fy, gz = (double)fz;
+        vx = kick(vx, p.hdt, gx);
+        vy = kick(vy, p.hdt, gy);
+        vz = kick(vz, p.hdt, gz);
+        if (kEnergy) {
+            v[2] = (vx * vx + vy * vy) + vz * vz;
+            v[3] = vx;
+            v[4] = vy;
+            v[5] = vz;
+        }
+        vx = kick(vx, p.hdt, gx);
+        vy = kick(vy, p.hdt, gy);
+        vz = kick(vz, p.hdt, gz);
+        x = wrap(drift(x, p.dt, vx), p.L);
+        y = wrap(drift(y, p.dt, vy), p.L);
+        z = wrap(drift(z, p.dt, vz), p.L);
+        const int c = cell_of_pos(x, y, z, p);
+        const int rank = atomicAdd(&pw.cell_count[c], 1);
+        // (scratch_view: with kCopy p.s* are the state arrays)
+        p.sx[i] = x;
+        p.sy[i] = y;
+        p.sz[i] = z;
+        pw.vx[i] = vx;
+        pw.vy[i] = vy;
+        pw.vz[i] = vz;
+        if (kCopy) pw.id[i] = p.id[i];
+        pw.cell_of[i] = c;
+        pw.slot[i] = rank;
+        if (!isfinite(v[0] + gx + gy + gz)) atomicOr(&p.dev->flags, (int)MD_FLAG_NONFINITE);
+    }
+    if (!kEnergy) return;
+    block_sum<6>(v, red);
+    if (threadIdx.x == 0) {
+        p.fpart[2 * wg.id] = v[0];
+        p.fpart[2 * wg.id + 1] = v[1];
+        double* const kp = step_part(p);
+        for (int c = 0; c < 4; ++c) kp[c * (int64_t)p.nblk_force + wg.id] = v[2 + c];
+    }
+}
+
+template <typename F, bool kCopy>
+__global__ void k_cells_step(Single b)
+{
+    __shared__ double red[(1024 / kWave) * 6];
+    const Wg wg{(int)blockIdx.x, (int)gridDim.x};
+    if (b.p.dev->record)
+        cells_step<F, kCopy, true>(b.p, wg, red);
+    else
+        cells_step<F, kCopy, false>(b.p, wg, red);
 }
 
 template <typename F, typename Acc, class B>
@@ -552,13 +642,13 @@ static void forces_seq(const B& b, const LaunchShape& sh, hipStream_t s, int fla
         const dim3 g(sh.grid[G_TILES]), t(sh.block);
         const bool copy = (flags & kFoldCopy) && sh.reorder;
         if (sh.precision == MD_FP64 && copy)
-            hipLaunchKernelGGL((k_forces_cells<double, AccD, B, true>), g, t, 0, s, b);
+            hipLaunchKernelGGL((k_forces_cells<double, B, true>), g, t, 0, s, b);
         else if (sh.precision == MD_FP64)
-            hipLaunchKernelGGL((k_forces_cells<double, AccD, B, false>), g, t, 0, s, b);
+            hipLaunchKernelGGL((k_forces_cells<double, B, false>), g, t, 0, s, b);
         else if (copy)
-            hipLaunchKernelGGL((k_forces_cells<float, AccF, B, true>), g, t, 0, s, b);
+            hipLaunchKernelGGL((k_forces_cells<float, B, true>), g, t, 0, s, b);
         else
-            hipLaunchKernelGGL((k_forces_cells<float, AccF, B, false>), g, t, 0, s, b);
+            hipLaunchKernelGGL((k_forces_cells<float, B, false>), g, t, 0, s, b);
         return;
     }
     if (sh.precision == MD_FP64)
@@ -604,6 +694,18 @@ void launch_forces(const Batch& b, const LaunchShape& sh, hipStream_t s) { force
 void launch_forces_step(const KParams& p, hipStream_t s)
 {
     const Single b{p};
+    if (p.mode == MD_CELLS_ONLY) {
+        const dim3 g(grid_of(p, G_TILES)), t(p.block);
+        if (p.precision == MD_FP64 && p.reorder)
+            hipLaunchKernelGGL((k_cells_step<double, true>), g, t, 0, s, b);
+        else if (p.precision == MD_FP64)
+            hipLaunchKernelGGL((k_cells_step<double, false>), g, t, 0, s, b);
+        else if (p.reorder)
+            hipLaunchKernelGGL((k_cells_step<float, true>), g, t, 0, s, b);
+        else
+            hipLaunchKernelGGL((k_cells_step<float, false>), g, t, 0, s, b);
+        return;
+    }
     if (p.precision == MD_FP64)
         step_seq<double>(b, shape_of(p), s);
     else

@@ -311,6 +311,19 @@ __host__ __device__ inline bool nl_small(const KParams& p)
 
 LaunchShape shape_of(const KParams& p);
 
+// The partials of a recorded fused force pass, v^2, Px, Py, Pz (component c of
+// workgroup w at [c nblk_force + w]): in the region of the integration's partials
+// when they fit it, else behind the workgroups' U, W.
+__host__ __device__ inline bool step_part_in_ipart(const KParams& p)
+{
+    return p.nblk_force <= 2 * kIntegrateGridMax;
+}
+
+__device__ __forceinline__ double* step_part(const KParams& p)
+{
+    return step_part_in_ipart(p) ? p.ipart : p.fpart + 2 * (int64_t)p.nblk_force;
+}
+
 // Largest number of force-pass workgroups any tuning can ask for (the
 // cells-only pass takes kCellLanes lanes per atom, workgroups of at least 64).
 inline int64_t max_force_blocks(int64_t n, int64_t ncell)
@@ -333,7 +346,9 @@ void launch_layer_forces(const KParams& p, hipStream_t s);
 void launch_layer_export(const KParams& p, int32_t* out, hipStream_t s);
 void launch_layer_reorder(const KParams& p, hipStream_t s);
 void launch_cell_scan(const KParams& p, hipStream_t s);
-void launch_sort_small_finish(const KParams& p, int phase, int record_every, hipStream_t s);
+// launch_integrate_finish, then launch_cells(flags): one launch for a small system.
+void launch_finish_cells(const KParams& p, int flags, int phase, int record_every, bool fused,
+                         hipStream_t s);
 int allpairs_home_blocks(int n);
 void allpairs_split(int n, int* split, int* chunk);
 void launch_allpairs_forces(const KParams& p, hipStream_t s);
@@ -359,8 +374,13 @@ constexpr int kFoldCopy = 2;
 // arrays.
 constexpr int kFoldBin = 4;
 constexpr int kSortSmallOk = 8;
+// A system of at most kSortSmall atoms whose tables fit its LDS builds its
+// cells in one workgroup (k_cells_lds).  The line: an atom fits 14 bits beside
+// its cell, and past it the tables no longer fit 144 KiB; one CU's memory path
+// makes the rebuild itself slower than the whole chip's from about 5000 atoms
+// on, but idle steps (11 of 12) cost 2 us against 8.
 constexpr int kSortSmall = 16384;
-void launch_cells(const KParams& p, int force, hipStream_t s);
+void launch_cells(const KParams& p, int flags, hipStream_t s);
 void launch_neighbors(const KParams& p, int force, hipStream_t s);
 void launch_nl_export(const KParams& p, int32_t* out, hipStream_t s);
 void launch_forces(const KParams& p, hipStream_t s, int flags = 0);
@@ -388,17 +408,19 @@ void launch_integrate_finish(const KParams& p, int phase, int record_every, hipS
 // The force pass of a step with the integration pass that follows it (phase
 // 1): each home atom's force is used where it is summed, so neither the
 // forces nor the old positions pass through memory.  The drifted positions go
-// to the scratch arrays, since other tiles still read the old ones: the next
-// kernels take flip_positions of p.  Tiled lists with reorder (which have the
-// scratch arrays), no third law, no bonded terms; fused_fits: its partials of a
-// recorded step (K, P per tile, behind the tiles' U, W) fit the partials'
-// region.
+// to the scratch arrays, since other workgroups still read the old ones: the
+// next kernels take flip_positions of p (a cells-only system with reorder
+// excepted: its pass reads the sorted scratch arrays and writes the state).
+// fused_fits: the tiled pipeline with scratch positions, no third law, no bonded
+// terms, and room for the partials of a recorded step (K, P per workgroup).
 inline bool fused_fits(const KParams& p)
 {
-    return p.pipeline == MD_PIPE_TILED && p.mode == MD_NEIGHBOR_LIST && p.reorder &&
-           !p.newton3 && !p.bonded_on &&
-           6ll * p.n_tiles <= 2ll * max_force_blocks(p.n, p.ncell);
+    return p.pipeline == MD_PIPE_TILED && p.sx && !p.newton3 && !p.bonded_on &&
+           (p.mode == MD_CELLS_ONLY || p.reorder) &&
+           (step_part_in_ipart(p) || 6ll * p.nblk_force <= 2ll * max_force_blocks(p.n, p.ncell));
 }
+// whether a fused pass leaves the positions in the scratch arrays
+inline bool fused_flips(const KParams& p) { return !(p.mode == MD_CELLS_ONLY && p.reorder); }
 void launch_forces_step(const KParams& p, hipStream_t s);
 void launch_forces_step(const Batch& b, const LaunchShape& sh, hipStream_t s);
 void launch_integrate_pass(const Batch& b, const LaunchShape& sh, int phase, hipStream_t s,

@@ -17,6 +17,15 @@ CASES = {
     "wca_fp32": dict(n=6000, rho=0.7, r_cut=WCA, dt=0.005, precision="fp32"),
     "lj": dict(n=5324, rho=0.8442, r_cut=2.5, dt=0.004),
     "lj_four_cells": dict(n=1500, rho=0.8, r_cut=2.5, dt=0.004),
+    # cells only: without and with reorder, tables in LDS and past it (16 000
+    # atoms), more atoms than one workgroup sorts
+    "cells": dict(n=4001, rho=0.8, r_cut=WCA, dt=0.005, neighbor_list=False),
+    "cells_reorder_fp32": dict(n=2500, rho=0.7, r_cut=WCA, dt=0.005, neighbor_list=False,
+                               reorder=True, precision="fp32"),
+    "cells_16000": dict(n=16000, rho=0.8, r_cut=WCA, dt=0.005, neighbor_list=False),
+    "cells_20000_reorder": dict(n=20000, rho=0.8, r_cut=WCA, dt=0.005, neighbor_list=False,
+                                reorder=True),
+    "cells_lj": dict(n=4000, rho=0.8442, r_cut=2.5, dt=0.004, neighbor_list=False, block=64),
     "lj_mass_eps": dict(n=4000, rho=0.8, r_cut=2.5, dt=0.004, eps=1.3, mass=2.0),
 }
 
