@@ -19,6 +19,8 @@
 // forces the build), so a step's launch sequence is fixed.  Each kernel is a
 // template over where its parameters come from (one system, or one replica
 // of a batch: md_internal.h).
+#include <type_traits>
+
 #include "md_finish.h"
 
 namespace md {
@@ -53,12 +55,8 @@ __global__ void k_clear(B b)
     }
 }
 
-template <class B>
-__global__ void k_bin(B b, int force)
+__device__ __forceinline__ void bin_atoms(const KParams& p, const Wg& wg)
 {
-    Wg wg;
-    KParams p;
-    if (!b.fetch_gated(G_ATOMS, force, wg, p)) return;
     for (int i0 = wg.id * blockDim.x; i0 < p.n; i0 += wg.n * blockDim.x) {
         const int i = i0 + threadIdx.x;
         const bool act = i < p.n;
@@ -76,6 +74,40 @@ __global__ void k_bin(B b, int force)
         }
         rank_in_cell(p, act, c, i);
     }
+}
+
+template <class B>
+__global__ void k_bin(B b, int force)
+{
+    Wg wg;
+    KParams p;
+    if (!b.fetch_gated(G_ATOMS, force, wg, p)) return;
+    bin_atoms(p, wg);
+}
+
+// k_bin behind a fused force pass, with the finish of that pass: every
+// workgroup takes the rebuild decision itself from the sixteen displacement
+// maxima (one load), the first one also counts and records the step
+// (finish_step, which leaves the maxima for the others; the scan after it
+// clears them).  Saves the finish's launch, 4.3 us of a 42 us step at 256 000 atoms.
+__global__ __launch_bounds__(1024) void k_bin_finish(Single b, int record_every)
+{
+    const KParams& p = b.p;
+    const Wg wg{(int)blockIdx.x, (int)gridDim.x};
+    bool rebuild;
+    if (wg.id == 0) {
+        __shared__ double red[(1024 / kWave) * 5];
+        rebuild = finish_step(p, 1, record_every, true, red, false);
+    } else {
+        __shared__ int rb;
+        if (threadIdx.x < kWave) {
+            const double m = step_dmax2(p);
+            if (threadIdx.x == 0) rb = m > p.disp_thr2 ? 1 : 0;
+        }
+        __syncthreads();
+        rebuild = rb != 0;
+    }
+    if (rebuild) bin_atoms(p, wg);
 }
 
 // The cell offsets: one workgroup of kScanThreads threads scans the counts
@@ -162,16 +194,117 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(B b, int force)
 {
     Wg wg;
     KParams p;
+    if constexpr (std::is_same_v<B, Single>)  // see k_bin_finish
+        if (threadIdx.x < kDmaxSlots) b.p.dev->dmax_slot[threadIdx.x] = 0;
     if (!b.fetch_gated(G_ONE, force, wg, p)) return;
     __shared__ int wsum[kScanThreads / kWave];
     scan_cells(p, wsum);
 }
 
+// The scan of a system with many cells, spread over workgroups of one chunk of
+// scan_chunk(p) cells each: the counts become offsets inside the chunk, in
+// place, and the chunk's total and largest count go to p.ipart (free between
+// the finish and the next integration); k_scatter adds the chunks before.  One
+// workgroup walking all cells is a chain of loads and barriers, about 1 us per
+// 4096 cells: 28 us at 110 592 cells (256 000 WCA atoms), where this takes 4.
+constexpr int kScanChunksMax = 1024;
+
+__host__ __device__ inline int scan_chunk(const KParams& p)
+{
+    constexpr int unit = kScanThreads * kScanPer;
+    const int n = (int)(((int64_t)p.ncell + unit - 1) / unit);  // chunks of one round
+    return ((n + kScanChunksMax - 1) / kScanChunksMax) * unit;
+}
+__host__ __device__ inline int scan_chunks(const KParams& p)
+{
+    const int c = scan_chunk(p);
+    return (int)(((int64_t)p.ncell + c - 1) / c);
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_scan_part(Single b, int force)
+{
+    const KParams& p = b.p;
+    if (blockIdx.x == 0 && threadIdx.x < kDmaxSlots) p.dev->dmax_slot[threadIdx.x] = 0;
+    if (!rebuild_on(p, force)) return;
+    __shared__ int wsum[kScanThreads / kWave];
+    const int chunk = scan_chunk(p), first = (int)blockIdx.x * chunk;
+    const int last = p.ncell - first < chunk ? p.ncell : first + chunk;
+    int carry = 0, m = 0;
+    for (int c0 = first; c0 < last; c0 += kScanThreads * kScanPer) {
+        const int c = c0 + threadIdx.x * kScanPer;
+        int v[kScanPer], sum = 0;
+        if (c + kScanPer <= last) {
+            const int4 q = *reinterpret_cast<const int4*>(p.cell_count + c);
+            v[0] = q.x;
+            v[1] = q.y;
+            v[2] = q.z;
+            v[3] = q.w;
+        } else {
+#pragma unroll
+            for (int k = 0; k < kScanPer; ++k) v[k] = c + k < last ? p.cell_count[c + k] : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < kScanPer; ++k) {
+            sum += v[k];
+            m = v[k] > m ? v[k] : m;
+        }
+        int total;
+        int ex = carry + workgroup_scan_excl(sum, wsum, total);
+        if (c + kScanPer <= last) {
+            *reinterpret_cast<int4*>(p.cell_count + c) =
+                make_int4(ex, ex + v[0], ex + v[0] + v[1], ex + v[0] + v[1] + v[2]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < kScanPer; ++k) {
+                if (c + k < last) p.cell_count[c + k] = ex;
+                ex += v[k];
+            }
+        }
+        carry += total;
+    }
+    m = workgroup_max(m);
+    if (threadIdx.x == 0) {
+        int* const part = reinterpret_cast<int*>(p.ipart);
+        part[blockIdx.x] = carry;
+        part[kScanChunksMax + blockIdx.x] = m;
+    }
+}
+
+// The atoms before each chunk of k_scan_part, into LDS (by the whole
+// workgroup); the first workgroup also publishes the largest occupancy.
+__device__ __forceinline__ void chunk_starts(const KParams& p, const Wg& wg, int* pre)
+{
+    const int* part = reinterpret_cast<const int*>(p.ipart);
+    const int n = scan_chunks(p);
+    if (threadIdx.x < kWave) {
+        const int lane = threadIdx.x;
+        int carry = 0, m = 0;
+        for (int c = lane; c - lane < n; c += kWave) {
+            const int v = c < n ? part[c] : 0;
+            if (wg.id == 0 && c < n) {
+                const int o = part[kScanChunksMax + c];
+                m = o > m ? o : m;
+            }
+            const int inc = wave_scan_incl(v);
+            if (c < n) pre[c] = carry + inc - v;
+            carry += __builtin_amdgcn_readlane(inc, kWave - 1);
+        }
+        if (wg.id == 0) {
+            m = wave_max(m);
+            if (lane == 0) {
+                p.dev->max_occ = m;
+                p.dev->max_nl = 0;
+            }
+        }
+    }
+    __syncthreads();
+}
+
 // Slot q of atom i in cell order (in the order the atomics gave), with its
 // permanent id beside it for the in-cell rank.
-__device__ __forceinline__ void scatter_atom(const KParams& p, int i)
+__device__ __forceinline__ void scatter_atom(const KParams& p, int i, int start)
 {
-    const int q = p.cell_start[p.cell_of[i]] + p.slot[i];
+    const int q = start + p.slot[i];
     p.tmp[q] = i;
     p.tmp[p.n + q] = p.id[i];  // the ids of a cell side by side
 }
@@ -214,24 +347,42 @@ __device__ __forceinline__ void sort_slot(const KParams& p, int q)
     }
 }
 
-template <class B>
+// kPart: behind k_scan_part; also writes the final cell_start.
+template <class B, bool kPart>
 __global__ void k_scatter(B b, int force)
 {
     Wg wg;
     KParams p;
     if (!b.fetch_gated(G_ATOMS, force, wg, p)) return;
-    for (int i = wg.id * blockDim.x + threadIdx.x; i < p.n; i += wg.n * blockDim.x)
-        scatter_atom(p, i);
+    const int i0 = wg.id * blockDim.x + threadIdx.x, stride = wg.n * blockDim.x;
+    if constexpr (kPart) {
+        __shared__ int pre[kScanChunksMax];
+        chunk_starts(p, wg, pre);
+        const int chunk = scan_chunk(p);
+        for (int i = i0; i < p.n; i += stride) {
+            const int c = p.cell_of[i];
+            scatter_atom(p, i, p.cell_count[c] + pre[c / chunk]);
+        }
+        for (int c = i0; c < p.ncell; c += stride)
+            p.cell_start[c] = p.cell_count[c] + pre[c / chunk];
+        if (i0 == 0) p.cell_start[p.ncell] = p.n;
+    } else {
+        for (int i = i0; i < p.n; i += stride) scatter_atom(p, i, p.cell_start[p.cell_of[i]]);
+    }
 }
 
+// clear: also clears the counts for the next binning (which k_scan does
+// itself).
 template <typename F, class B, Permute kPermute>
-__global__ void k_cellsort(B b, int force)
+__global__ void k_cellsort(B b, int force, int clear)
 {
     Wg wg;
     KParams p;
     if (!b.fetch_gated(G_ATOMS, force, wg, p)) return;
-    for (int q = wg.id * blockDim.x + threadIdx.x; q < p.n; q += wg.n * blockDim.x)
-        sort_slot<F, kPermute>(p, q);
+    const int i0 = wg.id * blockDim.x + threadIdx.x, stride = wg.n * blockDim.x;
+    for (int q = i0; q < p.n; q += stride) sort_slot<F, kPermute>(p, q);
+    if (clear)
+        for (int c = i0; c < p.ncell; c += stride) p.cell_count[c] = 0;
 }
 
 // Small systems (at most kSortSmall atoms): the scan, the scatter and the
@@ -257,7 +408,8 @@ __global__ __launch_bounds__(kScanThreads) void k_sort_small(B b, int force, int
     __shared__ int wsum[kScanThreads / kWave];
     scan_cells(p, wsum);
     __syncthreads();
-    for (int i = threadIdx.x; i < p.n; i += blockDim.x) scatter_atom(p, i);
+    for (int i = threadIdx.x; i < p.n; i += blockDim.x)
+        scatter_atom(p, i, p.cell_start[p.cell_of[i]]);
     __syncthreads();
     for (int q = threadIdx.x; q < p.n; q += blockDim.x) sort_slot<F, kPermute>(p, q);
 }
@@ -518,7 +670,7 @@ static void cells_seq(const B& b, const LaunchShape& sh, int flags, hipStream_t 
     const int force = flags & 1;
     const bool copy = !(flags & kFoldCopy);  // else the list or force pass copies back
     const dim3 atoms(sh.grid[G_ATOMS]), blk(sh.block);
-    if (!(flags & kFoldBin)) hipLaunchKernelGGL(k_bin<B>, atoms, blk, 0, s, b, force);
+    if (!(flags & (kFoldBin | kBinDone))) hipLaunchKernelGGL(k_bin<B>, atoms, blk, 0, s, b, force);
     if (n_small) {  // one system of at most kSortSmall atoms
         const dim3 one(1), t(kScanThreads);
         if (!sh.reorder)
@@ -534,16 +686,35 @@ static void cells_seq(const B& b, const LaunchShape& sh, int flags, hipStream_t 
             hipLaunchKernelGGL((k_sort_small<float, B, P_ALL, false>), one, t, 0, s, b, force, 0,
                                0, 0);
     } else {
-        hipLaunchKernelGGL(k_scan<B>, dim3(sh.grid[G_ONE]), dim3(kScanThreads), 0, s, b, force);
-        hipLaunchKernelGGL(k_scatter<B>, atoms, blk, 0, s, b, force);
+        bool part = false;
+        if constexpr (std::is_same_v<B, Single>) {
+            // more cells than one round of the one-workgroup scan (fewer would
+            // only add chunk_starts to it)
+            part = scan_chunks(b.p) > 1;
+            if (part) {
+                hipLaunchKernelGGL(k_scan_part, dim3(scan_chunks(b.p)), dim3(kScanThreads), 0, s,
+                                   b, force);
+                hipLaunchKernelGGL((k_scatter<B, true>), atoms, blk, 0, s, b, force);
+            }
+        }
+        const int clear = part ? 1 : 0;
+        if (!part) {
+            hipLaunchKernelGGL(k_scan<B>, dim3(sh.grid[G_ONE]), dim3(kScanThreads), 0, s, b,
+                               force);
+            hipLaunchKernelGGL((k_scatter<B, false>), atoms, blk, 0, s, b, force);
+        }
         if (!sh.reorder)
-            hipLaunchKernelGGL((k_cellsort<double, B, P_NONE>), atoms, blk, 0, s, b, force);
+            hipLaunchKernelGGL((k_cellsort<double, B, P_NONE>), atoms, blk, 0, s, b, force,
+                               clear);
         else if (!copy)
-            hipLaunchKernelGGL((k_cellsort<double, B, P_STATE>), atoms, blk, 0, s, b, force);
+            hipLaunchKernelGGL((k_cellsort<double, B, P_STATE>), atoms, blk, 0, s, b, force,
+                               clear);
         else if (sh.precision == MD_FP64)
-            hipLaunchKernelGGL((k_cellsort<double, B, P_ALL>), atoms, blk, 0, s, b, force);
+            hipLaunchKernelGGL((k_cellsort<double, B, P_ALL>), atoms, blk, 0, s, b, force,
+                               clear);
         else
-            hipLaunchKernelGGL((k_cellsort<float, B, P_ALL>), atoms, blk, 0, s, b, force);
+            hipLaunchKernelGGL((k_cellsort<float, B, P_ALL>), atoms, blk, 0, s, b, force,
+                               clear);
     }
     if (sh.reorder && copy) {
         if (sh.precision == MD_FP64)
@@ -590,6 +761,13 @@ void launch_finish_cells(const KParams& p, int flags, int phase, int record_ever
         else
             hipLaunchKernelGGL((k_sort_small<double, Single, P_NONE, true>), one, t, 0, s, b, 1,
                                phase, record_every, fused ? 1 : 0);
+        return;
+    }
+    if (fused && phase == 1 && p.mode == MD_NEIGHBOR_LIST) {
+        const int t = p.block > kFinishThreads ? p.block : kFinishThreads;
+        hipLaunchKernelGGL(k_bin_finish, dim3(grid_of(p, G_ATOMS)), dim3(t), 0, s, Single{p},
+                           record_every);
+        launch_cells(p, flags | kBinDone, s);
         return;
     }
     launch_integrate_finish(p, phase, record_every, s, fused);

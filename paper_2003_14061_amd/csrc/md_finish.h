@@ -93,13 +93,24 @@ __device__ __forceinline__ void record_step(const KParams& p, int n_wg, int reco
     }
 }
 
+// The largest squared displacement of a fused force pass (in every lane; a whole
+// wave calls it).
+__device__ __forceinline__ double step_dmax2(const KParams& p)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    double v = 0.0;
+    if (lane < kDmaxSlots) v = __longlong_as_double((long long)p.dev->dmax_slot[lane]);
+    return wave_max(v);
+}
+
 // The end of an integration pass: count the step and record it (phase >= 1),
 // and from the largest displacement decide whether the cells and list are
 // rebuilt before the next force pass (phase <= 1; returned in every thread).  By one workgroup of at
 // least kFinishThreads threads (red: LDS, (blockDim / 64) * 5 doubles).  fused:
-// the pass was a fused force pass (launch_forces_step).
+// the pass was a fused force pass (launch_forces_step), whose displacement maxima
+// are then cleared for the next one unless `clear` is false.
 __device__ __forceinline__ bool finish_step(const KParams& p, int phase, int record_every,
-                                            bool fused, double* red)
+                                            bool fused, double* red, bool clear = true)
 {
     bool rebuild = false;
     const int n_wg = grid_of(p, G_INTEGRATE);
@@ -109,13 +120,8 @@ __device__ __forceinline__ bool finish_step(const KParams& p, int phase, int rec
         double m = 0.0;
         if (fused) {
             if (threadIdx.x < kWave) {
-                unsigned long long* slot = p.dev->dmax_slot;
-                double v = 0.0;
-                if (threadIdx.x < kDmaxSlots) {
-                    v = __longlong_as_double((long long)slot[threadIdx.x]);
-                    slot[threadIdx.x] = 0;
-                }
-                m = wave_max(v);
+                m = step_dmax2(p);
+                if (clear && threadIdx.x < kDmaxSlots) p.dev->dmax_slot[threadIdx.x] = 0;
             }
         } else {
             m = finish_max<kFinishThreads>(p.ipart, n_wg, 8, 4, red);

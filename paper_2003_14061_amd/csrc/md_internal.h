@@ -374,6 +374,7 @@ constexpr int kFoldCopy = 2;
 // arrays.
 constexpr int kFoldBin = 4;
 constexpr int kSortSmallOk = 8;
+constexpr int kBinDone = 16;  // k_bin_finish has binned the atoms
 // A system of at most kSortSmall atoms whose tables fit its LDS builds its
 // cells in one workgroup (k_cells_lds).  The line: an atom fits 14 bits beside
 // its cell, and past it the tables no longer fit 144 KiB; one CU's memory path
