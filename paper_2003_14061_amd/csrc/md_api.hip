@@ -124,9 +124,7 @@ static void plan_tiles(md_ctx* c)
     else
         k.nblk_force = force_blocks(k);
     // list build: a lane per home atom of a mean tile (25% spare), or waves
-    // taking the home cells in turn: 8 waves from 8 home cells on, else 4 (a
-    // multiple of the CU's four SIMDs measured best: 6 or 12 waves for 12
-    // cells were 28-35% slower than 8 or 4)
+    // taking the home cells in turn: 8 waves from 8 home cells on, else 4
     k.nl_method = c->nl_method_req != MD_NL_AUTO ? c->nl_method_req
                                                  : (occ < 8.0 ? MD_NL_LANES : MD_NL_CELL_WAVES);
     const int home_cells = k.kx_max * k.ky_max * k.kz_max;
@@ -135,11 +133,17 @@ static void plan_tiles(md_ctx* c)
         waves = (int)ceil(1.25 * home_cells * occ / kWave);
         waves = waves > 16 ? 16 : waves;
     } else {
-        waves = home_cells >= 8 ? 8 : (home_cells >= 4 ? 4 : home_cells);
+        // few tiles, which leave room on the CUs: a wave per home cell of a tile of
+        // 12 (100 003 LJ atoms, 486 tiles: 60 against 76 us; 2.048M, 8640 tiles:
+        // 723 against 668 us, as two such workgroups share a CU instead of three)
+        waves = home_cells >= 12 && c->min_tiles > 0 && k.n_tiles < 3 * 256
+                    ? 12
+                    : (home_cells >= 8 ? 8 : (home_cells >= 4 ? 4 : home_cells));
     }
     waves = waves < 1 ? 1 : waves;
     const int nlb = c->nl_block_req > 0 ? c->nl_block_req : kWave * waves;
     k.nl_block = nlb < kWave ? kWave : (nlb > 1024 ? 1024 : nlb);
+    k.nl_queue = nl_queue_fits(k, k.nl_method, k.nl_block, c->lds_limit);
 }
 
 void replan_tiles(md_ctx* c) { plan_tiles(c); }
@@ -293,6 +297,8 @@ extern "C" md_status md_init(const md_params* in, md_ctx** out)
     k.inv_w = (double)nc / p.L;
     k.rc2 = p.r_cut * p.r_cut;
     k.rl2 = r_list * r_list;
+    k.box_reach2 = k.rl2 * (1.0 + 1e-9);
+    k.box_slack = 1e-6 * p.L;
     k.sig2 = p.sigma * p.sigma;
     k.eps2 = 2.0 * p.eps;
     k.eps48 = 48.0 * p.eps;
@@ -310,15 +316,6 @@ extern "C" md_status md_init(const md_params* in, md_ctx** out)
     k.dt = p.dt;
     k.disp_thr2 = (0.5 * p.skin) * (0.5 * p.skin);
     k.mass = p.mass;
-    // the minimum-image shortcut of the force pass needs partners closer than L/2
-    const double reach = r_list + p.skin;
-    if (nl && 2.0 * reach < 0.999 * p.L) {
-        k.inner_lo = reach;
-        k.inner_hi = p.L - reach;
-    } else {
-        k.inner_lo = 1.0;
-        k.inner_hi = 0.0;  // empty range: always take the minimum image
-    }
     k.block = p.block;
     // 2 lanes per atom (2.048 M-atom LJ, 512-thread workgroups: FP64 force pass
     // 255 us at 2 lanes, 267 at 4, 356 at 8; FP32-mixed 228, 244, 324)

@@ -304,9 +304,9 @@ __device__ __forceinline__ void chunk_starts(const KParams& p, const Wg& wg, int
 // permanent id beside it for the in-cell rank.
 __device__ __forceinline__ void scatter_atom(const KParams& p, int i, int start)
 {
-    const int q = start + p.slot[i];
+    const int q = start + p.slot[i], key = p.id[i];
     p.tmp[q] = i;
-    p.tmp[p.n + q] = p.id[i];  // the ids of a cell side by side
+    p.tmp[p.n + q] = key;  // the ids of a cell side by side
 }
 
 // Canonical order inside each cell: ascending permanent id.  The atom at
@@ -321,26 +321,41 @@ template <typename F, Permute kPermute>
 __device__ __forceinline__ void sort_slot(const KParams& p, int q)
 {
     const int32_t* ids = p.tmp + p.n;  // ids in slot order (scatter_atom)
-    const int s = p.tmp[q];
+    const int s = p.tmp[q], key = ids[q];
     const int c = p.cell_of[s];
+    // every load before the first store (the compiler may not reorder them)
+    double x, y, z, vx, vy, vz;
+    F fx, fy, fz;
+    if (kPermute != P_NONE) {
+        x = p.x[s];
+        y = p.y[s];
+        z = p.z[s];
+        vx = p.vx[s];
+        vy = p.vy[s];
+        vz = p.vz[s];
+        if (kPermute == P_ALL) {
+            fx = static_cast<const F*>(p.fx)[s];
+            fy = static_cast<const F*>(p.fy)[s];
+            fz = static_cast<const F*>(p.fz)[s];
+        }
+    }
     const int a = p.cell_start[c], cnt = p.cell_start[c + 1] - a;
-    const int key = ids[q];
     int rank = 0;
 #pragma unroll 4
     for (int j = 0; j < cnt; ++j) rank += ids[a + j] < key ? 1 : 0;
     const int d = a + rank;
     p.order[d] = s;
-    if (kPermute) {
-        p.sx[d] = p.x[s];
-        p.sy[d] = p.y[s];
-        p.sz[d] = p.z[s];
-        p.svx[d] = p.vx[s];
-        p.svy[d] = p.vy[s];
-        p.svz[d] = p.vz[s];
+    if (kPermute != P_NONE) {
+        p.sx[d] = x;
+        p.sy[d] = y;
+        p.sz[d] = z;
+        p.svx[d] = vx;
+        p.svy[d] = vy;
+        p.svz[d] = vz;
         if (kPermute == P_ALL) {
-            reinterpret_cast<F*>(p.sfx)[d] = static_cast<const F*>(p.fx)[s];
-            reinterpret_cast<F*>(p.sfy)[d] = static_cast<const F*>(p.fy)[s];
-            reinterpret_cast<F*>(p.sfz)[d] = static_cast<const F*>(p.fz)[s];
+            reinterpret_cast<F*>(p.sfx)[d] = fx;
+            reinterpret_cast<F*>(p.sfy)[d] = fy;
+            reinterpret_cast<F*>(p.sfz)[d] = fz;
         }
         p.sid[d] = key;
         p.scell[d] = c;
@@ -643,17 +658,23 @@ __global__ void k_copyback(B b, int force)
     KParams p;
     if (!b.fetch_gated(G_ATOMS, force, wg, p)) return;
     for (int q = wg.id * blockDim.x + threadIdx.x; q < p.n; q += wg.n * blockDim.x) {
-        p.x[q] = p.sx[q];
-        p.y[q] = p.sy[q];
-        p.z[q] = p.sz[q];
-        p.vx[q] = p.svx[q];
-        p.vy[q] = p.svy[q];
-        p.vz[q] = p.svz[q];
-        static_cast<F*>(p.fx)[q] = reinterpret_cast<const F*>(p.sfx)[q];
-        static_cast<F*>(p.fy)[q] = reinterpret_cast<const F*>(p.sfy)[q];
-        static_cast<F*>(p.fz)[q] = reinterpret_cast<const F*>(p.sfz)[q];
-        p.id[q] = p.sid[q];
-        p.cell_of[q] = p.scell[q];
+        const double x = p.sx[q], y = p.sy[q], z = p.sz[q];
+        const double vx = p.svx[q], vy = p.svy[q], vz = p.svz[q];
+        const F fx = reinterpret_cast<const F*>(p.sfx)[q];
+        const F fy = reinterpret_cast<const F*>(p.sfy)[q];
+        const F fz = reinterpret_cast<const F*>(p.sfz)[q];
+        const int id = p.sid[q], c = p.scell[q];
+        p.x[q] = x;
+        p.y[q] = y;
+        p.z[q] = z;
+        p.vx[q] = vx;
+        p.vy[q] = vy;
+        p.vz[q] = vz;
+        static_cast<F*>(p.fx)[q] = fx;
+        static_cast<F*>(p.fy)[q] = fy;
+        static_cast<F*>(p.fz)[q] = fz;
+        p.id[q] = id;
+        p.cell_of[q] = c;
         p.order[q] = q;
     }
 }

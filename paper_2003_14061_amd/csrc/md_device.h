@@ -384,14 +384,18 @@ template <bool kCopy>
 __device__ __forceinline__ void copy_home(const KParams& q, int k)
 {
     if (!kCopy) return;
-    q.sx[k] = q.x[k];
-    q.sy[k] = q.y[k];
-    q.sz[k] = q.z[k];
-    q.svx[k] = q.vx[k];
-    q.svy[k] = q.vy[k];
-    q.svz[k] = q.vz[k];
-    q.sid[k] = q.id[k];
-    q.scell[k] = q.cell_of[k];
+    // every load before the first store (the compiler may not reorder them)
+    const double x = q.x[k], y = q.y[k], z = q.z[k];
+    const double vx = q.vx[k], vy = q.vy[k], vz = q.vz[k];
+    const int id = q.id[k], c = q.cell_of[k];
+    q.sx[k] = x;
+    q.sy[k] = y;
+    q.sz[k] = z;
+    q.svx[k] = vx;
+    q.svy[k] = vy;
+    q.svz[k] = vz;
+    q.sid[k] = id;
+    q.scell[k] = c;
     q.order[k] = k;
 }
 

@@ -52,7 +52,8 @@ struct KParams {
     double ushift;          // half_shift / eps2: the shift in the units of the u sums
     double ushift2;         // 2 ushift = shift / (2 eps): the constant of the lean sums
     double eps, sigma;
-    double inner_lo, inner_hi;  // atoms with every coordinate in [lo, hi] need no minimum image
+    double box_reach2, box_slack;  // the list build's box test: past the list radius
+                                   // squared and past a bound rounded to FP32
     // state (caller-owned)
     double *x, *y, *z, *vx, *vy, *vz;
     void *fx, *fy, *fz;
@@ -85,6 +86,7 @@ struct KParams {
     int32_t int_grid;       // workgroups of the grid-stride per-atom kernels
     int32_t gate_grid;      // most workgroups of a rebuild-gated per-atom or per-cell kernel
     int32_t nl_method;      // MD_NL_LANES or MD_NL_CELL_WAVES
+    int32_t nl_queue;       // the list build's LDS holds the cell waves' queues
     // tiling of the neighbor-list mode: blocks of cells, the grid cut into
     // tiles_x x tiles_y x tiles_z near-equal blocks of at most kx_max x ky_max x
     // kz_max cells
@@ -393,6 +395,7 @@ void launch_forces(const Batch& b, const LaunchShape& sh, hipStream_t s);
 void launch_integrate(const Batch& b, const LaunchShape& sh, int phase, int record_every,
                       hipStream_t s);
 size_t nl_lds_bytes(const KParams& p);
+int nl_queue_fits(const KParams& p, int nl_method, int nl_block, size_t lds);
 size_t force_lds_bytes(const KParams& p);
 int force_blocks(const KParams& p);  // workgroups of the force pass for the current tuning
 // phase 0: kick + drift; 1: kick, record, kick + drift; 2: kick, record

@@ -31,7 +31,16 @@
 
 namespace md {
 
-__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+// The lane, opaque to the compiler, taken anew for each home cell: the many
+// addresses and masks formed from it would otherwise be computed once for all
+// cells and spilled, a scratch store of about 160 bytes per lane and wave (more
+// than the list itself).
+__device__ __forceinline__ int cell_lane()
+{
+    int lane = threadIdx.x & (kWave - 1);
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
 
 __device__ __forceinline__ double readlane_f64(double v, int lane)
 {
@@ -40,8 +49,29 @@ __device__ __forceinline__ double readlane_f64(double v, int lane)
     return __hiloint2double(hi, lo);
 }
 
-// LDS bytes of the list build: the staged tile.
-size_t nl_lds_bytes(const KParams& p) { return stage_bytes(p, p.scap); }
+// The common cell-wave build (nl_home_cell_q): rounds of 64 candidates in
+// registers (the first kRoundsLo always, the others when they hold any) and the
+// candidates tested at a time; a wave's LDS holds the queue with a gather round
+// past it, then in its place one list: at most kQueue hits behind an incomplete
+// chunk, with their padding.
+constexpr int kRoundsQ = 6, kRoundsLo = 4;
+constexpr int kQueue = kRoundsQ * kWave;
+constexpr size_t kCellWaveLds = 2 * (kQueue + kWave);
+
+// LDS bytes of the list build: the staged tile, and with nl_queue the queues
+// of the workgroup's waves.
+size_t nl_lds_bytes(const KParams& p)
+{
+    return stage_bytes(p, p.scap) + (p.nl_queue ? kCellWaveLds * (size_t)(p.nl_block / kWave) : 0);
+}
+
+// The queues go with the cell-wave build of full lists, where they fit: a
+// workgroup of nl_block threads in lds bytes (1 KiB spare for static LDS).
+int nl_queue_fits(const KParams& p, int nl_method, int nl_block, size_t lds)
+{
+    return nl_method == MD_NL_CELL_WAVES && !p.newton3 && p.mode == MD_NEIGHBOR_LIST &&
+           stage_bytes(p, p.scap) + kCellWaveLds * (size_t)(nl_block / kWave) + 1024 <= lds;
+}
 
 // Staged cell of column a - 1 in the row (dz, dy) = (sg / 3 - 1, sg % 3 - 1)
 // next to home cell home_t (at column a): the first cell of window sg.
@@ -55,11 +85,11 @@ __device__ __forceinline__ int window_cell(const Stage& s, int home_t, int sg)
 __device__ __forceinline__ int home_cell(const Stage& s, int hc)
 {
     const int a = 1 + hc % s.kx, r = hc / s.kx;
-    return home_row_cell(s, r) + (a - 1);
+    return uniform(home_row_cell(s, r) + (a - 1));
 }
 
 // The lists of home cell hc's atoms, by one wave; wmax: the longest list of
-// this lane's home atoms so far.  The candidates (the 9 windows of three cells
+// this wave's home atoms so far.  The candidates (the 9 windows of three cells
 // next to it, concatenated, in canonical order) are taken kRounds x 64 at a
 // time: lane l holds candidate k0 + 64 r + l (position, wrap bits, encoded
 // entry) in registers.  Each home atom hh in turn is broadcast from lane hh
@@ -68,11 +98,11 @@ __device__ __forceinline__ int home_cell(const Stage& s, int hc)
 // lanes), m_hh being hh's running list length, kept in a scalar register while
 // hh is tested and in lane hh of a vector register between blocks.  Lanes past
 // the candidates read the home cell's first atom (e = hb) and never hit.
-template <int kImage, bool kHalf, bool kFits, bool kCopy, int kRounds, bool kFull>
+template <int kImage, bool kHalf, bool kFits, int kRounds, bool kFull>
 __device__ __forceinline__ void nl_home_cell(const KParams& p, const Stage& s, int hc, bool small,
                                              int& wmax)
 {
-    const int lane = threadIdx.x & (kWave - 1);
+    const int lane = cell_lane();
     const int home_t = home_cell(s, hc);
     // table values are the same in every lane: keep them in scalar registers
     const int hb = uniform(s.off[home_t]), he = uniform(s.off[home_t + 1]);
@@ -204,19 +234,270 @@ __device__ __forceinline__ void nl_home_cell(const KParams& p, const Stage& s, i
                 mreg = lane == hh ? (int)m_h : mreg;
             }
         }
-        // lengths, sentinel padding of the last chunk, displacement references
+        // lengths, sentinel padding of the last chunk
         if (home_lane) {
             const int stored = mreg < (int)cap ? mreg : (int)cap;
             p.nl_count[slot_l] = stored;
             uint16_t* base = nl16 + (int64_t)slot_l * kChunk;
             for (int mm = stored; mm % kChunk != 0; ++mm)
                 base[(int64_t)(mm / kChunk) * npad4 + mm % kChunk] = (uint16_t)s.total;
-            p.xr[slot_l] = hx;
-            p.yr[slot_l] = hy;
-            p.zr[slot_l] = hz;
-            copy_home<kCopy>(p, slot_l);
         }
-        wmax = home_lane && mreg > wmax ? mreg : wmax;
+        const int longest = wave_max(home_lane ? mreg : 0);
+        wmax = longest > wmax ? longest : wmax;
+    }
+}
+
+// ---- the common cell-wave build: full lists, atoms staged in LDS, at least 5
+// cells per side ----
+//
+// Two phases per home cell, by one wave.  Gather: the candidates (the 9 windows
+// of three cells, in canonical order) that lie within the list radius of the
+// bounding box of the home cell's atoms go, in order, to a queue in LDS (of 533
+// candidates at the dense LJ state about 350 stay).  Test: up to kQueue queued
+// candidates at a time are held in registers, 64 per round; each home atom in
+// turn is tested against all rounds, the hits' entries go to their places in
+// a buffer in LDS, and from there whole 8-byte chunks are stored, a lane per
+// chunk.
+//
+// Bound by instruction issue, vector and scalar together (2.048M LJ atoms: 439 M
+// vector and 156 M scalar instructions in the earlier build, which tested all
+// 533 candidates and stored entry by entry).  Forced builds: 830 -> 668 us at
+// 2.048M LJ atoms, 91 -> 60 us at 100 003, 93 -> 70 us at 32 000, 38 -> 32 us at
+// 10 007.  Storing eight lists together, a row of their chunks as one run of 64
+// bytes, took an eighth of the write requests and was slower (817 us): requests
+// do not bound it.
+
+__device__ __forceinline__ void lds_order()
+{
+    // the wave's LDS operations complete in order; this keeps the compiler from
+    // moving them past each other
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Largest and smallest f over the wave's lanes, for values whose FP32 bits are
+// ordered as unsigned integers (f >= 0): one DPP instruction per step.
+__device__ __forceinline__ uint32_t wave_umax(uint32_t v)
+{
+    v = max(v, dpp_read<0x111, 0xf, false>(v, v));
+    v = max(v, dpp_read<0x112, 0xf, false>(v, v));
+    v = max(v, dpp_read<0x114, 0xf, false>(v, v));
+    v = max(v, dpp_read<0x118, 0xf, false>(v, v));
+    v = max(v, dpp_read<0x142, 0xa, false>(v, v));
+    v = max(v, dpp_read<0x143, 0xc, false>(v, v));
+    return from_lane63(v);
+}
+
+// Middle and half width, rounded outward past the FP32 conversion, of the
+// interval the lanes' v span (v > -L).
+__device__ __forceinline__ void wave_span(const KParams& p, double v, double& mid, double& half)
+{
+    const uint32_t b = __builtin_bit_cast(uint32_t, (float)(v + p.L));
+    const double hi = (double)__builtin_bit_cast(float, wave_umax(b)) - p.L;
+    const double lo = (double)__builtin_bit_cast(float, ~wave_umax(~b)) - p.L;
+    mid = 0.5 * (lo + hi);
+    half = 0.5 * (hi - lo) + p.box_slack;
+}
+
+// The image of candidate (cx, cy, cz) on the side of (bx, by, bz) in each
+// flagged coordinate (see image).
+__device__ __forceinline__ void near_image(const KParams& p, int fl, double bx, double by,
+                                           double bz, double& cx, double& cy, double& cz)
+{
+    if (fl & 1) cx += bx > cx ? p.L : -p.L;
+    if (fl & 2) cy += by > cy ? p.L : -p.L;
+    if (fl & 4) cz += bz > cz ? p.L : -p.L;
+}
+
+// The lists of home cell hc's atoms (see above).  q: this wave's LDS: the queue
+// and, once a block's candidates are in registers, one list in its place.
+// small, wmax as nl_home_cell.
+template <int kImage, bool kFull>
+__device__ __forceinline__ void nl_home_cell_q(const KParams& p, const Stage& s, int hc,
+                                               bool small, MD_LDS uint16_t* q, int& wmax)
+{
+    const int lane = cell_lane();
+    const int home_t = home_cell(s, hc);
+    const int hb = uniform(s.off[home_t]), he = uniform(s.off[home_t + 1]);
+    const int hslot0 = uniform(s.slot[home_t]);
+    MD_LDS uint64_t* const q64 = (MD_LDS uint64_t*)q;
+    const uint32_t cap = (uint32_t)p.cap;  // a multiple of 4
+    const uint32_t rowb = 8u * (uint32_t)p.npad;
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(p.nl64, 0, -1, kBufferWord3);
+    // slightly past the list radius: the box test rounds differently from the
+    // inclusion test and only has to keep whatever that one could accept
+    const double reach2 = p.box_reach2;
+    for (int h0 = hb; h0 < he; h0 += kWave) {
+        const int nhs = he - h0 < kWave ? he - h0 : kWave;
+        const bool home_lane = lane < nhs;
+        const int hl = h0 + (home_lane ? lane : 0);
+        const int slot_l = atom_at(p, hslot0 + (hl - hb));
+        double bx, by, bz, wx, wy, wz;  // the home atoms' box: middle, half widths
+        {
+            double hx, hy, hz;
+            lds_xyz(s.p3, hl, hx, hy, hz);
+            wave_span(p, hx, bx, wx);
+            wave_span(p, hy, by, wy);
+            wave_span(p, hz, bz, wz);
+        }
+        int mreg = 0;        // lane hh: home atom hh's list length so far
+        uint64_t part = 0;   // lane hh: its last, incomplete chunk
+        int qn = 0;          // candidates queued
+        int sg = 0, e0 = 0, ee = 0, t0 = 0;  // window being gathered: entries e0 .. ee - 1 left
+        bool more = true;
+        while (more) {
+            // gather until the queue is full or the windows end
+            while (qn < kQueue) {
+                if (e0 >= ee) {
+                    if (sg == 9) break;
+                    t0 = window_cell(s, home_t, sg);
+                    e0 = uniform(s.off[t0]);
+                    ee = uniform(s.off[t0 + 3]);
+                    ++sg;
+                    continue;
+                }
+                const int e = e0 + lane;
+                const int ev = e < ee ? e : hb;
+                double cx, cy, cz;
+                lds_xyz(s.p3, ev, cx, cy, cz);
+                int fl = 0;
+                if (kImage == 1) {
+                    const int t = t0 + (e >= s.off[t0 + 1] ? 1 : 0) + (e >= s.off[t0 + 2] ? 1 : 0);
+                    fl = e < ee ? s.flag[t] : 0;
+                    near_image(p, fl, bx, by, bz, cx, cy, cz);
+                }
+                const double dx = fmax(fabs(cx - bx) - wx, 0.0);
+                const double dy = fmax(fabs(cy - by) - wy, 0.0);
+                const double dz = fmax(fabs(cz - bz) - wz, 0.0);
+                // (a NaN position stays: under the inclusion test it never hits)
+                const int left = ee - e0;
+                const uint64_t in = left >= kWave ? ~0ull : (1ull << left) - 1ull;
+                const uint64_t mk =
+                    in & ~__builtin_amdgcn_ballot_w64(dist2(dx, dy, dz) > reach2);
+                if (__builtin_amdgcn_inverse_ballot_w64(mk)) {
+                    const uint32_t m = __builtin_amdgcn_mbcnt_hi(
+                        (uint32_t)(mk >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mk, (uint32_t)qn));
+                    q[m] = (uint16_t)((uint32_t)e | ((uint32_t)fl << kEntryBits));
+                }
+                qn += (int)__popcll(mk);
+                e0 += kWave;
+            }
+            more = e0 < ee || sg < 9 || qn > kQueue;
+            const int nb = qn < kQueue ? qn : kQueue;  // candidates of this block
+            lds_order();
+            double cx[kRoundsQ], cy[kRoundsQ], cz[kRoundsQ];
+            uint32_t enc[kRoundsQ];
+#pragma unroll
+            for (int r = 0; r < kRoundsQ; ++r) {
+                const int k = r * kWave + lane;
+                const uint32_t v = q[k];  // past nb: whatever was there, inside the staging
+                enc[r] = k < nb ? v : (uint32_t)hb;
+            }
+            const uint16_t rest = q[kQueue + lane];  // gathered past this block (none, or few)
+#pragma unroll
+            for (int r = 0; r < kRoundsQ; ++r) {
+                lds_xyz(s.p3, (int)(enc[r] & kEntryMask), cx[r], cy[r], cz[r]);
+                if (kImage == 1)
+                    near_image(p, (int)(enc[r] >> kEntryBits), bx, by, bz, cx[r], cy[r], cz[r]);
+                if (r * kWave + lane >= nb) cx[r] = __builtin_nan("");  // never near
+            }
+            lds_order();
+            for (int hh = 0; hh < nhs; ++hh) {
+                double xi, yi, zi;
+                lds_xyz(s.p3, h0 + hh, xi, yi, zi);  // one read the whole wave shares
+                const uint32_t m0 = (uint32_t)__builtin_amdgcn_readlane(mreg, hh);
+                const uint32_t slot = (uint32_t)__builtin_amdgcn_readlane(slot_l, hh);
+                uint64_t mk[kRoundsQ];
+                auto test = [&](int r) {
+                    const double dx = xi - cx[r], dy = yi - cy[r], dz = zi - cz[r];
+                    const double r2 = dist2(dx, dy, dz);
+                    mk[r] = __builtin_amdgcn_ballot_w64(r2 < p.rl2);
+                    // the image was taken before the difference: where that could
+                    // decide, once more as the inclusion test rounds it
+                    if (kImage == 1 &&
+                        __builtin_amdgcn_ballot_w64(fabs(r2 - p.rl2) < p.box_slack)) {
+                        double ex, ey, ez;
+                        lds_xyz(s.p3, (int)(enc[r] & kEntryMask), ex, ey, ez);
+                        ex = xi - ex;
+                        ey = yi - ey;
+                        ez = zi - ez;
+                        image<1>(p, (int)(enc[r] >> kEntryBits), ex, ey, ez);
+                        mk[r] = __builtin_amdgcn_ballot_w64(r2 == r2 && dist2(ex, ey, ez) < p.rl2);
+                    }
+                    // not the atom itself (its entry has no wrap bits)
+                    mk[r] &= __builtin_amdgcn_ballot_w64(enc[r] != (uint32_t)(h0 + hh));
+                };
+                // the hits of round r to the buffer from entry `at` on
+                auto place = [&](int r, uint32_t at) {
+                    MD_LDS uint16_t* const to = q + at;
+                    if (__builtin_amdgcn_inverse_ballot_w64(mk[r]))
+                        to[__builtin_amdgcn_mbcnt_hi(
+                            (uint32_t)(mk[r] >> 32),
+                            __builtin_amdgcn_mbcnt_lo((uint32_t)mk[r], 0u))] = (uint16_t)enc[r];
+                };
+                // (opaque, so that no address or value formed from them is kept across
+                // the loop: kept, they spill, and their reloads wait for every store in
+                // flight)
+                int nbs = nb, ln = lane, pad = uniform(s.total);
+                asm volatile("" : "+s"(nbs), "+v"(ln), "+s"(pad));
+                // independent tests first, then the hits, behind the incomplete chunk
+#pragma unroll
+                for (int r = 0; r < kRoundsLo; ++r) test(r);
+                uint32_t m = m0 % kChunk;
+                if (m != 0 && ln == hh) q64[0] = part;
+                lds_order();
+#pragma unroll
+                for (int r = 0; r < kRoundsLo; ++r) {
+                    place(r, m);
+                    m += (uint32_t)__popcll(mk[r]);
+                }
+                if (nbs > kRoundsLo * kWave) {
+#pragma unroll
+                    for (int r = kRoundsLo; r < kRoundsQ; ++r) test(r);
+#pragma unroll
+                    for (int r = kRoundsLo; r < kRoundsQ; ++r) {
+                        place(r, m);
+                        m += (uint32_t)__popcll(mk[r]);
+                    }
+                }
+                // the whole chunks to rows m0 / 4 ..; in the last block the rest too,
+                // padded with the sentinel
+                uint32_t n = m / kChunk;
+                if (!more) {
+                    if (ln < kChunk) q[m + ln] = (uint16_t)pad;
+                    n = (m + kChunk - 1) / kChunk;
+                }
+                lds_order();
+                const uint32_t row0 = m0 / kChunk, rows = cap / kChunk;
+                for (uint32_t c0 = 0; c0 < n; c0 += kWave) {
+                    const uint32_t c = c0 + ln;
+                    if (c < n && row0 + c < rows) {  // past the capacity: not kept
+                        const uint64_t ch = q64[c];
+                        if (!kFull || small) {
+                            typedef int v2i __attribute__((ext_vector_type(2)));
+                            __builtin_amdgcn_raw_buffer_store_b64(
+                                __builtin_bit_cast(v2i, ch), rsrc, (int)((uint32_t)ln * rowb),
+                                (int)((row0 + c0) * rowb + 8u * slot), 0);
+                        } else {
+                            p.nl64[(int64_t)(row0 + c) * p.npad + slot] = ch;
+                        }
+                    }
+                }
+                if (more) {
+                    const uint64_t ch = q64[n];
+                    part = ln == hh ? ch : part;
+                }
+                lds_order();
+                const uint32_t len = m0 / kChunk * kChunk + m;
+                mreg = ln == hh ? (int)len : mreg;
+                wmax = (int)len > wmax ? (int)len : wmax;
+            }
+            q[lane] = rest;
+            lds_order();
+            qn -= nb;
+        }
+        if (home_lane) p.nl_count[slot_l] = mreg < (int)cap ? mreg : (int)cap;
     }
 }
 
@@ -354,6 +635,22 @@ __device__ __forceinline__ void nl_tile(const KParams& p, int t, char* smem, int
         if (threadIdx.x == 0) atomicOr(&p.dev->flags, (int)MD_FLAG_NL_OVERFLOW);
         return;
     }
+    // cell waves: the displacement references and the folded copy-back of the
+    // tile's home atoms, a thread per atom, while the staging loads are under way
+    // (a lane per atom of the home cell at its end used a third of the lanes, one
+    // cell after the other: 190 us of a build at 2.048M LJ atoms)
+    if (kMethod != MD_NL_LANES) {
+        const int nh = home_count(s);
+        for (int h = threadIdx.x; h < nh; h += blockDim.x) {
+            int e, pos;
+            home_atom(s, h, e, pos);
+            const int k = atom_at(p, pos);
+            p.xr[k] = p.x[k];
+            p.yr[k] = p.y[k];
+            p.zr[k] = p.z[k];
+            copy_home<kCopy>(p, k);
+        }
+    }
     stage_positions(p, s);
     __syncthreads();
     const int mode = image_mode(p, tile_interior(p, g));
@@ -372,9 +669,12 @@ __device__ __forceinline__ void nl_tile(const KParams& p, int t, char* smem, int
         }
         return;
     }
-    const int wid = threadIdx.x / kWave, nw = blockDim.x / kWave;
+    const int wid = uniform((int)threadIdx.x / kWave), nw = blockDim.x / kWave;
     const int ncells = g.kx * g.ky * g.kz;
     const bool small = nl_small(p);
+    // this wave's queue and list buffer, behind the tables
+    MD_LDS uint16_t* const queue =
+        (MD_LDS uint16_t*)((MD_LDS char*)smem + stage_bytes(p, p.scap) + wid * kCellWaveLds);
     // Home cells next to a periodic boundary (real index 0 or nc - 1 on some
     // axis) have wrapped candidates and take the image rule; the other home
     // cells of a boundary tile have none and take the interior path.  The rare
@@ -385,25 +685,35 @@ __device__ __forceinline__ void nl_tile(const KParams& p, int t, char* smem, int
     for (int hc = wid; hc < ncells; hc += nw) {
         if (kFull && mode == 2) {
             if (s.fits)
-                nl_home_cell<2, kHalf, true, kCopy, 1, kFull>(p, s, hc, small, wmax);
+                nl_home_cell<2, kHalf, true, 1, kFull>(p, s, hc, small, wmax);
             else
-                nl_home_cell<2, kHalf, false, kCopy, 1, kFull>(p, s, hc, small, wmax);
+                nl_home_cell<2, kHalf, false, 1, kFull>(p, s, hc, small, wmax);
         } else if (!s.fits) {
-            nl_home_cell<1, kHalf, false, kCopy, 1, kFull>(p, s, hc, small, wmax);
+            nl_home_cell<1, kHalf, false, 1, kFull>(p, s, hc, small, wmax);
         } else if (mode == 0 || !home_wraps(p, g, hc)) {
-            nl_home_cell<0, kHalf, true, kCopy, kNlRounds, kFull>(p, s, hc, small, wmax);
+            if constexpr (kHalf) {
+                nl_home_cell<0, kHalf, true, kNlRounds, kFull>(p, s, hc, small, wmax);
+            } else if (p.nl_queue) {
+                nl_home_cell_q<0, kFull>(p, s, hc, small, queue, wmax);
+            } else {
+                nl_home_cell<0, kHalf, true, 1, kFull>(p, s, hc, small, wmax);
+            }
         } else {
-            nl_home_cell<1, kHalf, true, kCopy, kNlRounds, kFull>(p, s, hc, small, wmax);
+            if constexpr (kHalf) {
+                nl_home_cell<1, kHalf, true, kNlRounds, kFull>(p, s, hc, small, wmax);
+            } else if (p.nl_queue) {
+                nl_home_cell_q<1, kFull>(p, s, hc, small, queue, wmax);
+            } else {
+                nl_home_cell<1, kHalf, true, 1, kFull>(p, s, hc, small, wmax);
+            }
         }
     }
 }
 
-// The list build, gated by the rebuild flag.  Workgroups take tiles
-// v = id, id + n, ... (grid rule G_NL, one tile each at present: a capped grid
-// looping over tiles idles less per launch but measured slower per rebuild,
-// from the uneven tile counts of the last wave of workgroups); tile v keeps
-// the XCD-aware order (v mod 8 is the workgroup's XCD when n is a multiple
-// of 8).
+// The list build, gated by the rebuild flag: one workgroup per tile, in the
+// XCD-aware order (grid rule G_NL; a capped grid looping over tiles idles less
+// per launch but measured slower per rebuild, from the uneven tile counts of the
+// last wave of workgroups).
 // At most 80 VGPRs: six waves per SIMD, which the LDS of the dense LJ tiles
 // (three workgroups of eight waves per CU) allows.
 template <class B, int kMethod, bool kHalf, bool kCopy, bool kFull>
@@ -415,10 +725,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(6))) void k_nl_tiles(B b, int forc
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const KParams q = kCopy ? scratch_view(p) : p;
     int wmax = 0;
-    for (int v = wg.id; v < q.n_tiles; v += wg.n) {
-        nl_tile<kMethod, kHalf, kCopy, kFull>(q, xcd_tile(v, q.n_tiles), smem, wmax);
-        __syncthreads();  // the next tile reuses the LDS
-    }
+    nl_tile<kMethod, kHalf, kCopy, kFull>(q, xcd_tile(wg.id, wg.n), smem, wmax);
     // the longest list: one global atomic per workgroup
     const int mmax = workgroup_max(wmax);
     if (threadIdx.x == 0 && mmax > 0) {

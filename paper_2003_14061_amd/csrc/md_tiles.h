@@ -58,6 +58,9 @@ constexpr int kChunk = 4;                    // entries per 8-byte list chunk
 // data, no swizzle, the range check on the byte offset alone.
 constexpr int kBufferWord3 = 0x00020000;
 
+// A value that is the same in every lane of the wave, in a scalar register.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 struct Tile {
     int cx0, cy0, cz0, kx, ky, kz;
 };
@@ -87,6 +90,13 @@ __device__ __forceinline__ Tile tile_of(const KParams& p, int t)
     split_cells(p.nc, p.tiles_x, tx, g.cx0, g.kx);
     split_cells(p.nc, p.tiles_y, ty, g.cy0, g.ky);
     split_cells(p.nc, p.tiles_z, tz, g.cz0, g.kz);
+    // the same in every lane, but divided on the VALU: into scalar registers
+    g.cx0 = uniform(g.cx0);
+    g.cy0 = uniform(g.cy0);
+    g.cz0 = uniform(g.cz0);
+    g.kx = uniform(g.kx);
+    g.ky = uniform(g.ky);
+    g.kz = uniform(g.kz);
     return g;
 }
 
@@ -137,7 +147,7 @@ __host__ __device__ __forceinline__ int stage_table_ints(const KParams& p)
 
 // Dynamic LDS bytes of the staged tile: positions (and with `aux` a second
 // 3-vector) of cap atoms, then the cell tables.
-inline size_t stage_bytes(const KParams& p, int cap, bool aux = false)
+__host__ __device__ inline size_t stage_bytes(const KParams& p, int cap, bool aux = false)
 {
     return sizeof(double) * (aux ? 6 : 3) * (size_t)cap +
            sizeof(int) * (size_t)stage_table_ints(p);
@@ -222,8 +232,8 @@ __device__ __forceinline__ void stage_tables(const KParams& p, const Tile& g, St
         s.scan[0] = q1 <= g.kx + 1 ? q1 : s.stride;
         s.scan[1] = q1 + nc <= g.kx + 1 ? q1 + nc : s.stride;
     }
-    s.total = carry;
-    s.fits = carry < s.cap;
+    s.total = uniform(carry);
+    s.fits = s.total < s.cap;
     __syncthreads();
     // home rows r = (c - 1) ky + (b - 1): the prefix of their home atoms (one wave,
     // a row per lane, at most 64 rows)
