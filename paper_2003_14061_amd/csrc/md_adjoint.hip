@@ -100,7 +100,7 @@ struct AdjAcc {
 template <typename T>
 struct AdjOp {
     const KParams& p;
-    const Stage& s;
+    const MD_LDS double* a3;  // lambda_v of the staged atoms
     const AdjArgs& q;
     double lix, liy, liz;  // lambda_v of the home atom
     AdjAcc<T>& a;
@@ -110,7 +110,7 @@ struct AdjOp {
         if (!(r2 < p.rc2)) return;
         double ljx, ljy, ljz;
         if (j < 0) {
-            lds_xyz(s.a3, e, ljx, ljy, ljz);
+            lds_xyz(a3, e, ljx, ljy, ljz);
         } else {
             ljx = q.vx[j];
             ljy = q.vy[j];
@@ -142,22 +142,107 @@ struct AdjOp {
     }
 };
 
-template <typename T, int LANES>
-__global__ void k_adj_point(KParams p, AdjArgs q)
+template <int LANES, typename T>
+__device__ __forceinline__ void group_sum(AdjAcc<T>& a)
 {
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    __shared__ double red[(1024 / kWave) * 2];
-    const Tile g = tile_of(p, xcd_tile(blockIdx.x, gridDim.x));
+    if (LANES > 1) {
+        a.jx = lane_group_sum<LANES>(a.jx);
+        a.jy = lane_group_sum<LANES>(a.jy);
+        a.jz = lane_group_sum<LANES>(a.jz);
+        a.fx = lane_group_sum<LANES>(a.fx);
+        a.fy = lane_group_sum<LANES>(a.fy);
+        a.fz = lane_group_sum<LANES>(a.fz);
+        a.gx = lane_group_sum<LANES>(a.gx);
+        a.gy = lane_group_sum<LANES>(a.gy);
+        a.gz = lane_group_sum<LANES>(a.gz);
+        a.u = lane_group_sum<LANES>(a.u);
+        a.w = lane_group_sum<LANES>(a.w);
+        a.np = lane_group_sum<LANES>(a.np);
+    }
+}
+
+// What the point does with home atom i's sums; lu: the mean energy's weight.
+template <typename T>
+__device__ __forceinline__ void adj_end(const KParams& p, const AdjArgs& q, const AdjAcc<T>& a,
+                                        int i, double vix, double viy, double viz, double lu,
+                                        double (&th)[2])
+{
+    const double Fx = a.fx, Fy = a.fy, Fz = a.fz;
+    const double lx = q.lx[i] + q.coef * (double)a.jx - lu * Fx;
+    const double ly = q.ly[i] + q.coef * (double)a.jy - lu * Fy;
+    const double lz = q.lz[i] + q.coef * (double)a.jz - lu * Fz;
+    q.lx[i] = lx;
+    q.ly[i] = ly;
+    q.lz[i] = lz;
+    q.nx[i] = vix + q.drift * lx;
+    q.ny[i] = viy + q.drift * ly;
+    q.nz[i] = viz + q.drift * lz;
+    const double ui = p.eps2 * (double)a.u - p.half_shift * (double)a.np;
+    const double wi = 0.5 * (double)a.w;
+    th[0] += q.coef * (vix * Fx + viy * Fy + viz * Fz) / p.eps + lu * ui / p.eps;
+    th[1] += q.coef * (vix * (double)a.gx + viy * (double)a.gy + viz * (double)a.gz) +
+             lu * wi / p.sigma;
+    if (!isfinite(lx + ly + lz)) atomicOr(&p.dev->flags, (int)MD_FLAG_NONFINITE);
+}
+
+// A tile from its rows in registers, as forces_rows (md_forces.hip).
+template <typename T, int LANES>
+__device__ __forceinline__ void adj_rows(const KParams& p, const AdjArgs& q, const Rows& t,
+                                         char* smem, double lu, double (&th)[2])
+{
+    MD_LDS double* const p3 = (MD_LDS double*)smem;
+    MD_LDS double* const a3 = p3 + 3 * q.cap;
+    constexpr int kPer = kWave / LANES;
+    const int lane = threadIdx.x & (kWave - 1), sub = lane % LANES;
+    const int w0 = uniform((int)threadIdx.x / kWave) * kPer;
+    const int per_pass = (int)blockDim.x / LANES;
+    stage_rows<true>(p, t, p3, a3, q.vx, q.vy, q.vz);
+    bool staged = false;
+    for (int h0 = w0; h0 < t.nh || !staged; h0 += per_pass) {
+        const int h = h0 + lane / LANES;
+        int i = 0, eh = 0, cnt = 0;
+        uint64_t next = 0;
+        if (h0 < t.nh) {
+            int ds, de, row;
+            find_row<false>(t.hstart, t.d1 + t.e1 - t.hstart, t.e1 - t.hstart, h0, kPer, h, ds, de,
+                            row);
+            i = atom_at(p, h < t.nh ? h + ds : 0);
+            eh = h + de;
+            if (h < t.nh) {
+                cnt = p.nl_count[i];
+                if (sub <= p.cap / kChunk) next = p.nl64[(int64_t)sub * p.npad + i];
+            }
+        }
+        if (!staged) __syncthreads();
+        staged = true;
+        if (h0 >= t.nh) break;
+        AdjAcc<T> a;
+        double vix = 0.0, viy = 0.0, viz = 0.0;
+        if (h < t.nh) {
+            double xi, yi, zi;
+            lds_xyz(p3, eh, xi, yi, zi);
+            lds_xyz(a3, eh, vix, viy, viz);
+            AdjOp<T> op{p, a3, q, vix, viy, viz, a};
+            walk_staged<LANES>(p, p3, i, sub, cnt, next, xi, yi, zi, op);
+        }
+        group_sum<LANES>(a);
+        if (h < t.nh && sub == 0) adj_end(p, q, a, i, vix, viy, viz, lu, th);
+    }
+}
+
+// Any other tile, through the cell tables in LDS.
+template <typename T, int LANES>
+__device__ __forceinline__ void adj_tables(const KParams& p, const AdjArgs& q, const Tile& g,
+                                           char* smem, double lu, double (&th)[2])
+{
     Stage s = stage_layout(p, smem, q.cap, true);
     stage_tables(p, g, s);
     const int nh = home_count(s);
     const int mode = staged_image_mode(p, s, tile_interior(p, g));
     stage_atoms<true, true>(p, s, q.vx, q.vy, q.vz);
     __syncthreads();
-    const double lu = q.loss_scale != 0.0 ? q.gobs[0] * q.loss_scale : 0.0;
     const int per_pass = blockDim.x / LANES;
     const int sub = threadIdx.x % LANES;
-    double th[2] = {0.0, 0.0};
     for (int hb = 0; hb < nh; hb += per_pass) {
         const int h = hb + threadIdx.x / LANES;
         AdjAcc<T> a;
@@ -176,42 +261,29 @@ __global__ void k_adj_point(KParams p, AdjArgs q)
                 viy = q.vy[i];
                 viz = q.vz[i];
             }
-            AdjOp<T> op{p, s, q, vix, viy, viz, a};
+            AdjOp<T> op{p, s.a3, q, vix, viy, viz, a};
             walk_home<LANES>(p, s, mode, i, sub, p.nl_count[i], xi, yi, zi, op);
         }
-        if (LANES > 1) {
-            a.jx = lane_group_sum<LANES>(a.jx);
-            a.jy = lane_group_sum<LANES>(a.jy);
-            a.jz = lane_group_sum<LANES>(a.jz);
-            a.fx = lane_group_sum<LANES>(a.fx);
-            a.fy = lane_group_sum<LANES>(a.fy);
-            a.fz = lane_group_sum<LANES>(a.fz);
-            a.gx = lane_group_sum<LANES>(a.gx);
-            a.gy = lane_group_sum<LANES>(a.gy);
-            a.gz = lane_group_sum<LANES>(a.gz);
-            a.u = lane_group_sum<LANES>(a.u);
-            a.w = lane_group_sum<LANES>(a.w);
-            a.np = lane_group_sum<LANES>(a.np);
-        }
-        if (h < nh && sub == 0) {
-            const double Fx = a.fx, Fy = a.fy, Fz = a.fz;
-            const double lx = q.lx[i] + q.coef * (double)a.jx - lu * Fx;
-            const double ly = q.ly[i] + q.coef * (double)a.jy - lu * Fy;
-            const double lz = q.lz[i] + q.coef * (double)a.jz - lu * Fz;
-            q.lx[i] = lx;
-            q.ly[i] = ly;
-            q.lz[i] = lz;
-            q.nx[i] = vix + q.drift * lx;
-            q.ny[i] = viy + q.drift * ly;
-            q.nz[i] = viz + q.drift * lz;
-            const double ui = p.eps2 * (double)a.u - p.half_shift * (double)a.np;
-            const double wi = 0.5 * (double)a.w;
-            th[0] += q.coef * (vix * Fx + viy * Fy + viz * Fz) / p.eps + lu * ui / p.eps;
-            th[1] += q.coef * (vix * (double)a.gx + viy * (double)a.gy + viz * (double)a.gz) +
-                     lu * wi / p.sigma;
-            if (!isfinite(lx + ly + lz)) atomicOr(&p.dev->flags, (int)MD_FLAG_NONFINITE);
-        }
+        group_sum<LANES>(a);
+        if (h < nh && sub == 0) adj_end(p, q, a, i, vix, viy, viz, lu, th);
     }
+}
+
+template <typename T, int LANES>
+__global__ void k_adj_point(KParams p, AdjArgs q)
+{
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    __shared__ double red[(1024 / kWave) * 2];
+    const Tile g = tile_of(p, xcd_tile(blockIdx.x, gridDim.x));
+    const double lu = q.loss_scale != 0.0 ? q.gobs[0] * q.loss_scale : 0.0;
+    double th[2] = {0.0, 0.0};
+    bool rows = rows_fit(p) && p.nc >= 5;
+    if (rows) {
+        const Rows t = row_table(p, g);
+        rows = t.total < q.cap;
+        if (rows) adj_rows<T, LANES>(p, q, t, smem, lu, th);
+    }
+    if (!rows) adj_tables<T, LANES>(p, q, g, smem, lu, th);
     block_sum<2>(th, red);
     if (threadIdx.x == 0) {
         q.tpart[2 * blockIdx.x] = th[0];
@@ -248,12 +320,40 @@ __device__ __forceinline__ double gr_norm(const KParams& p, const GrArgs& g, int
 // Bins whose kernel reaches distance r: |r - r_b| < 3w.
 __device__ __forceinline__ void bin_range(const GrArgs& g, double r, int& b0, int& b1)
 {
-    const double delta = g.rmax / g.n_bins;
-    b0 = (int)floor((r - 3.0 * g.width) / delta - 0.5);
-    b1 = (int)ceil((r + 3.0 * g.width) / delta - 0.5);
+    b0 = (int)floor((r - 3.0 * g.width) * g.inv_delta - 0.5);
+    b1 = (int)ceil((r + 3.0 * g.width) * g.inv_delta - 0.5);
     b0 = b0 < 0 ? 0 : b0;
     b1 = b1 > g.n_bins - 1 ? g.n_bins - 1 : b1;
 }
+
+// The Gaussian exp(-t^2 / 2 w^2) at the bins of a pair in turn, t falling by one
+// bin width each: from one bin to the next it grows by a factor that itself
+// shrinks by a constant one, so a pair takes two exponentials instead of one per
+// bin (seven at a width of one bin).  Bins far wider than the kernel, where the
+// factor could overflow, take an exponential each.
+struct GrGauss {
+    double t, e, f;
+    __device__ __forceinline__ GrGauss(const GrArgs& g, double r, int b)
+    {
+        t = r - (b + 0.5) * g.delta;
+        at(g);
+        f = exp((t - 0.5 * g.delta) * g.delta * g.inv_w * g.inv_w);
+    }
+    __device__ __forceinline__ void at(const GrArgs& g)
+    {
+        e = exp(-0.5 * (t * g.inv_w) * (t * g.inv_w));
+    }
+    __device__ __forceinline__ void next(const GrArgs& g)
+    {
+        t -= g.delta;
+        if (g.chain) {
+            e *= f;
+            f *= g.fall;
+        } else {
+            at(g);
+        }
+    }
+};
 
 struct GrOp {
     const GrArgs& g;
@@ -262,15 +362,16 @@ struct GrOp {
     __device__ __forceinline__ void operator()(double, double, double, double r2, int, int)
     {
         if (!(r2 < reach2)) return;
-        const double r = sqrt(r2), w = g.width;
+        const double r = sqrt(r2);
         int b0, b1;
         bin_range(g, r, b0, b1);
+        GrGauss q(g, r, b0);
         for (int b = b0; b <= b1; ++b) {
-            const double t = r - bin_center(g, b);
-            if (fabs(t) < 3.0 * w) {
-                const double k = (exp(-0.5 * (t / w) * (t / w)) - exp(-4.5)) / (w * kSqrt2Pi);
+            if (fabs(q.t) < 3.0 * g.width) {
+                const double k = (q.e - g.edge) * g.norm;
                 atomicAdd(&lh[b], (unsigned long long)llrint(k * g.scale));
             }
+            q.next(g);
         }
     }
 };
@@ -279,6 +380,11 @@ __global__ void k_gr_clear(GrArgs g)
 {
     for (int b = threadIdx.x; b < g.n_bins; b += blockDim.x) g.hist[b] = 0ull;
 }
+
+// kGrLanes lanes share an atom's list: one lane per atom left three quarters of
+// the default workgroup idle on tiles of about 120 home atoms (32 000 LJ atoms:
+// 277 us, the gradient 294 us).
+constexpr int kGrLanes = 4;
 
 __global__ void k_gr_hist(KParams p, GrArgs g, int cap)
 {
@@ -294,13 +400,13 @@ __global__ void k_gr_hist(KParams p, GrArgs g, int cap)
     __syncthreads();
     const double reach = g.rmax + 3.0 * g.width;
     GrOp op{g, lh, reach * reach};
-    for (int h = threadIdx.x; h < nh; h += blockDim.x) {
+    for (int q = threadIdx.x; q < nh * kGrLanes; q += blockDim.x) {
         int eh, pos;
-        home_atom(s, h, eh, pos);
+        home_atom(s, q / kGrLanes, eh, pos);
         const int i = atom_at(p, pos);
         double xi, yi, zi;
         home_position(p, s, eh, i, xi, yi, zi);
-        walk_home<1>(p, s, mode, i, 0, p.nl_count[i], xi, yi, zi, op);
+        walk_home<kGrLanes>(p, s, mode, i, q % kGrLanes, p.nl_count[i], xi, yi, zi, op);
     }
     __syncthreads();
     for (int b = threadIdx.x; b < g.n_bins; b += blockDim.x)
@@ -326,15 +432,16 @@ struct GrGradOp {
                                                int)
     {
         if (!(r2 < reach2)) return;
-        const double r = sqrt(r2), w = g.width;
+        const double r = sqrt(r2);
         int b0, b1;
         bin_range(g, r, b0, b1);
         double c = 0.0;
+        GrGauss q(g, r, b0);
         for (int b = b0; b <= b1; ++b) {
-            const double t = r - bin_center(g, b);
-            if (fabs(t) < 3.0 * w)
-                c += wn[b] * (-(t / (w * w)) * exp(-0.5 * (t / w) * (t / w)) / (w * kSqrt2Pi));
+            if (fabs(q.t) < 3.0 * g.width) c -= wn[b] * (q.t * q.e);
+            q.next(g);
         }
+        c *= g.norm * g.inv_w * g.inv_w;
         const double f = 2.0 * c / r;
         ax += f * dx;
         ay += f * dy;
@@ -356,17 +463,27 @@ __global__ void k_gr_grad(KParams p, GrArgs g, int cap)
     stage_positions_imaged(p, s);
     __syncthreads();
     const double reach = g.rmax + 3.0 * g.width;
-    for (int h = threadIdx.x; h < nh; h += blockDim.x) {
-        int eh, pos;
-        home_atom(s, h, eh, pos);
-        const int i = atom_at(p, pos);
-        double xi, yi, zi;
-        home_position(p, s, eh, i, xi, yi, zi);
+    const int per_pass = blockDim.x / kGrLanes, sub = threadIdx.x % kGrLanes;
+    for (int hb = 0; hb < nh; hb += per_pass) {
+        const int h = hb + threadIdx.x / kGrLanes;
         GrGradOp op{g, wn, reach * reach};
-        walk_home<1>(p, s, mode, i, 0, p.nl_count[i], xi, yi, zi, op);
-        g.lx[i] = op.ax;
-        g.ly[i] = op.ay;
-        g.lz[i] = op.az;
+        int i = 0;
+        if (h < nh) {
+            int eh, pos;
+            home_atom(s, h, eh, pos);
+            i = atom_at(p, pos);
+            double xi, yi, zi;
+            home_position(p, s, eh, i, xi, yi, zi);
+            walk_home<kGrLanes>(p, s, mode, i, sub, p.nl_count[i], xi, yi, zi, op);
+        }
+        op.ax = lane_group_sum<kGrLanes>(op.ax);
+        op.ay = lane_group_sum<kGrLanes>(op.ay);
+        op.az = lane_group_sum<kGrLanes>(op.az);
+        if (h < nh && sub == 0) {
+            g.lx[i] = op.ax;
+            g.ly[i] = op.ay;
+            g.lz[i] = op.az;
+        }
     }
 }
 

@@ -161,6 +161,24 @@ static void relayout(md_ctx* c)
     c->ws_bytes = o;
 }
 
+// Second positions (the scratch positions) for the fused steps of a tiled system
+// without reorder, where the workspace stays within the static array's size (a
+// system that could be bound to it still can be; larger ones without reorder take
+// the separate integration pass); then lays the regions out.
+static void second_positions(md_ctx* c)
+{
+    const md_params& p = c->prm;
+    const bool wanted = !p.reorder && !p.newton3 && p.pipeline == MD_PIPE_TILED;
+    if (wanted) c->bytes[R_SX] = c->bytes[R_SY] = c->bytes[R_SZ] = 0;
+    relayout(c);
+    if (!wanted) return;
+    const size_t one = sizeof(double) * (size_t)p.n_atoms, more = 3 * align_up(one);
+    if (c->ws_bytes + more <= MD_STATIC_WORKSPACE_BYTES) {
+        c->bytes[R_SX] = c->bytes[R_SY] = c->bytes[R_SZ] = one;
+        relayout(c);
+    }
+}
+
 static md_status launched() { return hip_ok(hipGetLastError()); }
 
 static void drop_graph(md_ctx* c);  // md_step's captured graph (below)
@@ -258,23 +276,12 @@ extern "C" md_status md_init(const md_params* in, md_ctx** out)
     b[R_SX] = b[R_SY] = b[R_SZ] = b[R_SVX] = b[R_SVY] = b[R_SVZ] = perm * sizeof(double) * n;
     b[R_SFX] = b[R_SFY] = b[R_SFZ] = perm * fsz * n;
     b[R_SID] = b[R_SCELL] = perm * sizeof(int32_t) * n;
-    const bool cells2 = !nl && !perm && p.pipeline == MD_PIPE_TILED;
     b[R_APART] = ap_split > 1 ? fsz * 3 * (size_t)ap_split * npad : 0;
     const int64_t fblocks = max_force_blocks(n, ncell);
     b[R_FPART] = sizeof(double) * 2 * (size_t)(ap_blocks > fblocks ? ap_blocks : fblocks);
     b[R_IPART] = sizeof(double) * 8 * kIntegrateGridMax;
     b[R_HIST] = sizeof(md_record) * kHistCap;
-    relayout(c);
-    if (cells2) {
-        // second positions for the fused steps of a cells-only system without
-        // reorder, unless they would push the workspace past the static array
-        const size_t more = 3 * align_up(sizeof(double) * (size_t)n);
-        if (c->ws_bytes > MD_STATIC_WORKSPACE_BYTES ||
-            c->ws_bytes + more <= MD_STATIC_WORKSPACE_BYTES) {
-            b[R_SX] = b[R_SY] = b[R_SZ] = sizeof(double) * n;
-            relayout(c);
-        }
-    }
+    second_positions(c);
 
     KParams& k = c->kp;
     memset(&k, 0, sizeof(k));
@@ -339,7 +346,7 @@ extern "C" md_status md_set_bonded(md_ctx* c, const md_bonded* b)
     if (!b) {
         k.bonded_on = 0;
         c->bytes[R_SLOT_OF] = c->bytes[R_BPART] = 0;
-        relayout(c);
+        second_positions(c);
         return MD_OK;
     }
     const bool finite = isfinite(b->fene_k) && isfinite(b->fene_r0) && isfinite(b->bend_k) &&
@@ -359,7 +366,7 @@ extern "C" md_status md_set_bonded(md_ctx* c, const md_bonded* b)
     k.nblk_bonded = bonded_blocks(k.n);
     c->bytes[R_SLOT_OF] = sizeof(int32_t) * (size_t)k.n;
     c->bytes[R_BPART] = sizeof(double) * 2 * (size_t)k.nblk_bonded;
-    relayout(c);
+    second_positions(c);
     return MD_OK;
 }
 
@@ -1031,6 +1038,16 @@ static GrArgs gr_args(const md_ctx* c, const md_traj_params* tp, void* ws, const
     g.n_bins = tp->n_bins;
     g.rmax = tp->gr_rmax;
     g.width = tp->gr_width;
+    if (tp->n_bins > 0) {
+        const double dw = tp->gr_rmax / tp->n_bins / tp->gr_width;
+        g.delta = tp->gr_rmax / tp->n_bins;
+        g.inv_delta = tp->n_bins / tp->gr_rmax;
+        g.inv_w = 1.0 / tp->gr_width;
+        g.norm = 1.0 / (tp->gr_width * sqrt(2.0 * M_PI));
+        g.edge = exp(-4.5);
+        g.fall = exp(-dw * dw);
+        g.chain = dw <= 4.0;  // factors below exp(4 (3 + 4)), values above exp(-25)
+    }
     // fixed-point units: the largest possible bin sum (every atom, a full
     // list, each pair at the kernel's peak) stays below 2^62
     const double kmax = 1.0 / (tp->gr_width * sqrt(2.0 * M_PI));
@@ -1179,16 +1196,19 @@ extern "C" md_status md_traj_backward(md_ctx* c, const md_traj_params* tp, void*
         checkpoint_arrays(ws, L, seg, ck);
         if ((st = checkpoint(c, ck, false)) != MD_OK) return st;
         rebuild_all(c);
+        // (the drifted positions go straight to where they are kept)
+        KParams q = k;
         for (int j = 1; j < s1 - s0; ++j) {
-            launch_integrate_pass(k, j == 1 ? 0 : 1, sm);
-            launch_finish_cells(k, 0, j == 1 ? 0 : 1, 0, false, sm);
-            launch_neighbors(k, 0, sm);
-            launch_forces(k, sm);
-            for (int d = 0; d < 3; ++d)
-                if (hipMemcpyAsync(arr(ws, L, L.snap, (size_t)(j - 1) * 3 + d),
-                                   d == 0 ? k.x : (d == 1 ? k.y : k.z), sizeof(double) * n,
-                                   hipMemcpyDeviceToDevice, sm) != hipSuccess)
-                    return MD_ERR_HIP;
+            q.sx = arr(ws, L, L.snap, (size_t)(j - 1) * 3);
+            q.sy = arr(ws, L, L.snap, (size_t)(j - 1) * 3 + 1);
+            q.sz = arr(ws, L, L.snap, (size_t)(j - 1) * 3 + 2);
+            if (j == 1)
+                launch_integrate_pass(q, 0, sm, false, true);
+            else
+                launch_forces_step(q, sm);
+            flip_positions(q);
+            launch_finish_cells(q, 0, j == 1 ? 0 : 1, 0, j > 1, sm);
+            launch_neighbors(q, 0, sm);
         }
         // walk it backwards
         for (int s = s1 - 1; s >= s0; --s) {

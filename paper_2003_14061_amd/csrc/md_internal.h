@@ -128,6 +128,10 @@ struct GrArgs {
     double *ly, *lz;
     int32_t n_bins;
     double rmax, width, scale;  // scale: fixed-point units per unit of kernel value
+    double delta, inv_delta, inv_w, norm;  // bin width and its inverse, 1 / width, 1 / (width
+                                           // sqrt(2 pi))
+    double edge, fall;  // exp(-9/2), the kernel's value at 3 widths; exp(-(delta / width)^2)
+    int32_t chain;      // successive bins by factors (GrGauss)
 };
 
 // ---- where a workgroup's parameters come from ----
@@ -420,7 +424,6 @@ void launch_integrate_finish(const KParams& p, int phase, int record_every, hipS
 inline bool fused_fits(const KParams& p)
 {
     return p.pipeline == MD_PIPE_TILED && p.sx && !p.newton3 && !p.bonded_on &&
-           (p.mode == MD_CELLS_ONLY || p.reorder) &&
            (step_part_in_ipart(p) || 6ll * p.nblk_force <= 2ll * max_force_blocks(p.n, p.ncell));
 }
 // whether a fused pass leaves the positions in the scratch arrays
