@@ -161,14 +161,15 @@ static void relayout(md_ctx* c)
     c->ws_bytes = o;
 }
 
-// Second positions (the scratch positions) for the fused steps of a tiled system
-// without reorder, where the workspace stays within the static array's size (a
-// system that could be bound to it still can be; larger ones without reorder take
-// the separate integration pass); then lays the regions out.
+// Second positions (the scratch positions) for the fused steps of a cells-only
+// system without reorder, where the workspace stays within the static array's
+// size (a system that could be bound to it still can be; larger ones take the
+// separate integration pass); then lays the regions out.
 static void second_positions(md_ctx* c)
 {
     const md_params& p = c->prm;
-    const bool wanted = !p.reorder && !p.newton3 && p.pipeline == MD_PIPE_TILED;
+    const bool wanted =
+        p.mode == MD_CELLS_ONLY && !p.reorder && p.pipeline == MD_PIPE_TILED;
     if (wanted) c->bytes[R_SX] = c->bytes[R_SY] = c->bytes[R_SZ] = 0;
     relayout(c);
     if (!wanted) return;
@@ -1104,6 +1105,12 @@ extern "C" md_status md_traj_forward(md_ctx* c, const md_traj_params* tp, void* 
     // 32 000 atoms and 20-step segments: 59 against 49 us per step)
     const bool graph_on = c->graph_on;
     c->graph_on = false;
+    // second positions for the fused steps: lambda_x's place, unused until the
+    // reverse pass
+    KParams& k = c->kp;
+    k.sx = arr(ws, L, L.lam, 0);
+    k.sy = arr(ws, L, L.lam, 1);
+    k.sz = arr(ws, L, L.lam, 2);
     for (int seg = 0; seg < L.nseg && st == MD_OK; ++seg) {
         checkpoint_arrays(ws, L, seg, ck);
         if ((st = checkpoint(c, ck, true)) != MD_OK) break;
@@ -1111,6 +1118,7 @@ extern "C" md_status md_traj_forward(md_ctx* c, const md_traj_params* tp, void* 
         st = md_step(c, m, 1);
     }
     c->graph_on = graph_on;
+    k.sx = k.sy = k.sz = nullptr;  // (none of its own: reorder is off)
     if (st != MD_OK) return st;
     checkpoint_arrays(ws, L, L.nseg, ck);
     if ((st = checkpoint(c, ck, true)) != MD_OK) return st;
