@@ -52,8 +52,9 @@ struct KParams {
     double ushift;          // half_shift / eps2: the shift in the units of the u sums
     double ushift2;         // 2 ushift = shift / (2 eps): the constant of the lean sums
     double eps, sigma;
-    double box_reach2, box_slack;  // the list build's box test: past the list radius
-                                   // squared and past a bound rounded to FP32
+    double rl2_in, box_reach2;  // the list radius squared, less and more than the
+                                // roundings of a shifted image
+    double box_slack;           // past a bound rounded to FP32
     // state (caller-owned)
     double *x, *y, *z, *vx, *vy, *vz;
     void *fx, *fy, *fz;

@@ -526,7 +526,12 @@ __device__ __forceinline__ int home_column_cell(const Stage& s, int t1, int e)
 
 // The list of home atom h, by one lane.  Returns the number of entries found
 // (beyond the capacity: overflow).
-template <int kImage, bool kFits, bool kHalf, bool kCopy>
+//
+// Bound by instruction issue: nearly every candidate is a hit of some lane of the
+// wave, so the code of a hit counts as much as the test.  A hit shifts its entry
+// into the top of the chunk (two instructions); count and capacity are looked at
+// where a chunk is full.  Two candidates are read at a time.
+template <int kImage, bool kFits, bool kHalf>
 __device__ __forceinline__ int nl_home_atom(const KParams& p, const Stage& s, int h)
 {
     int e_self, pos_i, t1;
@@ -543,69 +548,106 @@ __device__ __forceinline__ int nl_home_atom(const KParams& p, const Stage& s, in
     }
     const uint32_t cap = (uint32_t)p.cap;  // a multiple of 4
     uint64_t* col = p.nl64 + slot_i;
-    uint64_t chunk = 0;
+    uint32_t lo = 0, hi = 0;  // the last four entries found, the newest on top
     uint32_t m = 0;
-    // An interior tile (kImage 0) has no wrapped cell: the three cells of a
-    // window are consecutive cells of one row, contiguous both among the staged
-    // atoms and in the cell-ordered slots, with no wrap bits, so each window is
-    // walked as one run (9 loops instead of 27).
-    constexpr int kRuns = kImage == 0 ? 1 : 3;
+    auto hit = [&](int e, int fl) {
+        const uint32_t v = (uint32_t)e | ((uint32_t)fl << kEntryBits);
+        lo = __builtin_amdgcn_alignbit(hi, lo, 16);
+        hi = __builtin_amdgcn_alignbit(v, hi, 16);
+        ++m;
+        if (m % kChunk == 0) {
+            if (m <= cap) *col = (uint64_t)hi << 32 | lo;
+            col += p.npad;
+        }
+    };
+    // Staged as periodic images (kShifted, see stage_atoms), or with no wrapped cell
+    // in the tile, the three cells of a window are one run of staged atoms whose raw
+    // separation is the minimum image; a shifted partner's differs from that of the
+    // wrap bits by roundings, so a pair within those of the list radius is decided by
+    // the wrap bits.
+    constexpr bool kShifted = kImage == 1 && kFits && !kHalf;
+    constexpr int kRuns = kImage == 0 || kShifted ? 1 : 3;
+    const double reach2 = kShifted ? p.box_reach2 : p.rl2;
     for (int sg = 0; sg < 9; ++sg) {
         const int tw = window_cell(s, home_t, sg);
 #pragma unroll
         for (int w = 0; w < kRuns; ++w) {
             const int t = tw + w;
-            const int eb = s.off[t], ee = s.off[t + (kImage == 0 ? 3 : 1)];
+            const int eb = s.off[t], ee = s.off[t + (kRuns == 1 ? 3 : 1)];
             const int fl = kImage == 0 ? 0 : s.flag[t];
-            const int tslot = kFits && !kHalf ? 0 : s.slot[t];
-            const uint64_t tag = (uint64_t)fl << kEntryBits;
-            if (kHalf && tslot + (ee - eb) <= pos_i) continue;
-            for (int e = eb; e < ee; ++e) {
-                double xj, yj, zj;
-                if (kFits) {
-                    lds_xyz(s.p3, e, xj, yj, zj);
-                } else {
-                    const int j = atom_at(p, tslot + (e - eb));
-                    xj = p.x[j];
-                    yj = p.y[j];
-                    zj = p.z[j];
+            if constexpr (kFits && !kHalf) {
+                int b1 = 0, b2 = 0, fl1 = 0, fl2 = 0;
+                if (kShifted) {
+                    b1 = s.off[t + 1];
+                    b2 = s.off[t + 2];
+                    fl1 = s.flag[t + 1];
+                    fl2 = s.flag[t + 2];
                 }
-                double dx = xi - xj, dy = yi - yj, dz = zi - zj;
-                image<kImage>(p, fl, dx, dy, dz);
-                const bool later = !kHalf || tslot + (e - eb) > pos_i;
-                if (later && dist2(dx, dy, dz) < p.rl2 && e != e_self) {
-                    if (m < cap) {
-                        chunk |= ((uint64_t)e | tag) << (16 * (m % kChunk));
-                        if (m % kChunk == kChunk - 1) {
-                            col[(int64_t)(m / kChunk) * p.npad] = chunk;
-                            chunk = 0;
+                for (int e0 = eb; e0 < ee; e0 += 2) {
+                    double r2[2];
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        double xj, yj, zj;
+                        lds_xyz(s.p3, e0 + u, xj, yj, zj);  // at most the sentinel's
+                        double dx = xi - xj, dy = yi - yj, dz = zi - zj;
+                        image<kShifted ? 0 : kImage>(p, fl, dx, dy, dz);
+                        r2[u] = dist2(dx, dy, dz);
+                    }
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const int e = e0 + u;
+                        bool in = r2[u] < reach2 && e != e_self && (u == 0 || e < ee);
+                        if (in) {
+                            const int f = !kShifted || e < b1 ? fl : (e < b2 ? fl1 : fl2);
+                            if (kShifted && r2[u] > p.rl2_in) {
+                                const int j = staged_slot(p, s, e);
+                                double dx = xi - p.x[j], dy = yi - p.y[j], dz = zi - p.z[j];
+                                image<1>(p, f, dx, dy, dz);
+                                in = dist2(dx, dy, dz) < p.rl2;
+                            }
+                            if (in) hit(e, f);
                         }
                     }
-                    ++m;
+                }
+            } else {
+                const int tslot = s.slot[t];
+                if (kHalf && tslot + (ee - eb) <= pos_i) continue;
+                for (int e = eb; e < ee; ++e) {
+                    double xj, yj, zj;
+                    if (kFits) {
+                        lds_xyz(s.p3, e, xj, yj, zj);
+                    } else {
+                        const int j = atom_at(p, tslot + (e - eb));
+                        xj = p.x[j];
+                        yj = p.y[j];
+                        zj = p.z[j];
+                    }
+                    double dx = xi - xj, dy = yi - yj, dz = zi - zj;
+                    image<kImage>(p, fl, dx, dy, dz);
+                    const bool later = !kHalf || tslot + (e - eb) > pos_i;
+                    if (later && dist2(dx, dy, dz) < p.rl2 && e != e_self) hit(e, fl);
                 }
             }
         }
     }
     const uint32_t stored = m < cap ? m : cap;
-    if (stored % kChunk != 0) {  // pad the last chunk with the sentinel
-        for (uint32_t mm = stored % kChunk; mm < kChunk; ++mm)
-            chunk |= (uint64_t)s.total << (16 * mm);
-        col[(int64_t)(stored / kChunk) * p.npad] = chunk;
+    if (m < cap && m % kChunk != 0) {  // pad the last chunk with the sentinel
+        for (uint32_t mm = m % kChunk; mm < kChunk; ++mm) {
+            lo = __builtin_amdgcn_alignbit(hi, lo, 16);
+            hi = __builtin_amdgcn_alignbit((uint32_t)s.total, hi, 16);
+        }
+        *col = (uint64_t)hi << 32 | lo;
     }
     p.nl_count[slot_i] = (int)stored;
-    p.xr[slot_i] = xi;
-    p.yr[slot_i] = yi;
-    p.zr[slot_i] = zi;
-    copy_home<kCopy>(p, slot_i);
     return (int)m;
 }
 
-template <int kImage, bool kFits, bool kHalf, bool kCopy>
+template <int kImage, bool kFits, bool kHalf>
 __device__ __forceinline__ void nl_lanes(const KParams& p, const Stage& s, int& wmax)
 {
     const int nh = home_count(s);
     for (int h = threadIdx.x; h < nh; h += blockDim.x) {
-        const int m = nl_home_atom<kImage, kFits, kHalf, kCopy>(p, s, h);
+        const int m = nl_home_atom<kImage, kFits, kHalf>(p, s, h);
         wmax = m > wmax ? m : wmax;
     }
 }
@@ -635,37 +677,38 @@ __device__ __forceinline__ void nl_tile(const KParams& p, int t, char* smem, int
         if (threadIdx.x == 0) atomicOr(&p.dev->flags, (int)MD_FLAG_NL_OVERFLOW);
         return;
     }
-    // cell waves: the displacement references and the folded copy-back of the
-    // tile's home atoms, a thread per atom, while the staging loads are under way
-    // (a lane per atom of the home cell at its end used a third of the lanes, one
-    // cell after the other: 190 us of a build at 2.048M LJ atoms)
-    if (kMethod != MD_NL_LANES) {
-        const int nh = home_count(s);
-        for (int h = threadIdx.x; h < nh; h += blockDim.x) {
-            int e, pos;
-            home_atom(s, h, e, pos);
-            const int k = atom_at(p, pos);
-            p.xr[k] = p.x[k];
-            p.yr[k] = p.y[k];
-            p.zr[k] = p.z[k];
-            copy_home<kCopy>(p, k);
-        }
+    // the displacement references and the folded copy-back of the tile's home atoms,
+    // a thread per atom, while the staging loads are under way (in cell waves a lane
+    // per atom of the home cell at its end used a third of the lanes, one cell after
+    // the other: 190 us of a build at 2.048M LJ atoms)
+    const int nh = home_count(s);
+    for (int h = threadIdx.x; h < nh; h += blockDim.x) {
+        int e, pos;
+        home_atom(s, h, e, pos);
+        const int k = atom_at(p, pos);
+        p.xr[k] = p.x[k];
+        p.yr[k] = p.y[k];
+        p.zr[k] = p.z[k];
+        copy_home<kCopy>(p, k);
     }
-    stage_positions(p, s);
+    if constexpr (kMethod == MD_NL_LANES && !kHalf)
+        stage_positions_imaged(p, s);
+    else
+        stage_positions(p, s);
     __syncthreads();
     const int mode = image_mode(p, tile_interior(p, g));
     if (kMethod == MD_NL_LANES) {
         if (kFull && mode == 2) {
             if (s.fits)
-                nl_lanes<2, true, kHalf, kCopy>(p, s, wmax);
+                nl_lanes<2, true, kHalf>(p, s, wmax);
             else
-                nl_lanes<2, false, kHalf, kCopy>(p, s, wmax);
+                nl_lanes<2, false, kHalf>(p, s, wmax);
         } else if (!s.fits) {
-            nl_lanes<1, false, kHalf, kCopy>(p, s, wmax);
+            nl_lanes<1, false, kHalf>(p, s, wmax);
         } else if (mode == 0) {
-            nl_lanes<0, true, kHalf, kCopy>(p, s, wmax);
+            nl_lanes<0, true, kHalf>(p, s, wmax);
         } else {
-            nl_lanes<1, true, kHalf, kCopy>(p, s, wmax);
+            nl_lanes<1, true, kHalf>(p, s, wmax);
         }
         return;
     }
