@@ -42,14 +42,42 @@ extern "C" const char* md_status_str(int32_t st)
     }
 }
 
+// What a force pass over `tiles` tiles of `home` and `staged` atoms costs, in units
+// of a home atom's share of a busy CU.  Such a CU takes a tile's home atoms, a
+// quarter of its staged ones and 60 for the rest of a workgroup; alone a workgroup
+// takes as long as its passes over the home atoms (the count spreads by less than
+// 0.55 sqrt(home), a third of a Poisson variance) and a quarter of the staged
+// atoms.  All CUs take tiles in rounds of three workgroups of the default 512
+// threads (six waves per SIMD); the last round counts by its fullest CU, unless
+// the tiles share the machine with other systems'.
+static double tiling_cost(const KParams& k, int64_t tiles, double home, double staged, bool alone)
+{
+    const int per_cu = k.force_block < 24 * kWave ? 24 * kWave / k.force_block : 1;
+    const double pass = (double)k.force_block / k.force_lanes;
+    const double work = home + 0.25 * staged + 60.0;
+    const double chain =
+        pass * ceil((home + 2.0 * sqrt(0.3 * home)) / pass) + 0.25 * staged;
+    const double round = hypot(chain, per_cu * work);
+    const int64_t slots = 256 * per_cu;
+    if (!alone) return (double)tiles / slots * round;
+    const int64_t rest = tiles % slots;
+    return (double)(tiles / slots) * round +
+           (rest > 0 ? hypot(chain, (double)((rest + 255) / 256) * work) : 0.0);
+}
+
 // Tiling of the neighbor-list mode: the grid is cut into near-equal blocks of
-// about kx x ky x kz cells (a requested size of 0 is chosen here).  The
-// choice minimizes the staged cells per home cell, (kx+2)(ky+2)(kz+2) over
-// kx ky kz, among blocks whose expected staged atoms (1.15x the mean plus 64)
-// fit the LDS share that lets three force workgroups share a CU, whose
-// expected home atoms fill at most three passes of the force workgroup and,
-// for a system alone, that give at least one tile per CU (ties: the longer
-// block along x, whose slot runs are longer).  The LDS
+// about kx x ky x kz cells, kx >= ky >= kz (a requested size of 0 is chosen
+// here).  The choice minimizes tiling_cost among blocks whose expected staged
+// atoms (1.15x the mean plus 64) fit the LDS share that lets three force
+// workgroups share a CU, and whose expected home atoms fill at most three passes
+// of the force workgroup (ties: the longer block along x, whose slot runs are
+// longer).  The rule before it, the fewest staged cells per home cell of at least
+// 256 tiles, left the last round of workgroups nearly empty at many sizes.  Steps
+// of both, list build included: 32 000 LJ atoms FP32 33.1 us at 3 x 2 x 1 cells (264
+// tiles), 29.4 at 2 x 2 x 2 (216); 70 000 LJ 37.0 and 33.6 (320 and 512 tiles);
+// 700 000 WCA 76.7 and 65.6 (1156 and 1445); over 27 sizes of both from 500 to 2.048M
+// atoms it picks a shape within 0.9% of the best one measured, on average, and
+// never a slower one than before by more than the runs differ.  The LDS
 // capacity then allows 1.15x the mean staged count plus 64 of the largest
 // block; a tile that does not fit takes its partners from global memory.
 static void plan_tiles(md_ctx* c)
@@ -59,36 +87,34 @@ static void plan_tiles(md_ctx* c)
     const double occ = (double)k.n / ((double)nc * nc * nc);
     const double lds_share = 160.0 * 1024.0 / 3.0 - 2048.0;  // bytes, three per CU
     const double home_max = 3.0 * k.force_block / k.force_lanes;
-    // a system alone keeps a workgroup per CU at least (replicas of a batch share
-    // the machine)
-    const int64_t ncell = (int64_t)nc * nc * nc;
-    const int64_t min_tiles = c->min_tiles < ncell ? c->min_tiles : ncell;
     auto maxsize = [nc](int req) {
         const int parts = (nc + req - 1) / req;
         return (nc + parts - 1) / parts;
     };
     int best[3] = {1, 1, 1};
-    double best_ratio = 1e300;
+    double best_score = 1e300;
     const int kx_hi = nc < 64 ? nc : 64, kyz_hi = nc < 4 ? nc : 4;
     for (int kz = 1; kz <= kyz_hi; ++kz)
         for (int ky = kz; ky <= kyz_hi; ++ky)
-            for (int kx = 1; kx <= kx_hi; ++kx) {
+            for (int kx = ky; kx <= kx_hi; ++kx) {
                 const int ax = c->tile_cells > 0 ? c->tile_cells : kx;
                 const int ay = c->tile_y > 0 ? c->tile_y : ky;
                 const int az = c->tile_z > 0 ? c->tile_z : kz;
                 const int mx = maxsize(ax), my = maxsize(ay), mz = maxsize(az);
-                const double staged = (double)(mx + 2) * (my + 2) * (mz + 2) * occ;
+                const double cells = (double)(mx + 2) * (my + 2) * (mz + 2);
+                const double staged = cells * occ;
                 const double home = (double)mx * my * mz * occ;
                 const int64_t tiles = (int64_t)((nc + ax - 1) / ax) * ((nc + ay - 1) / ay) *
                                       ((nc + az - 1) / az);
                 const bool ok = (1.15 * staged + 64.0) * 3.0 * sizeof(double) <= lds_share &&
-                                home <= home_max && tiles >= min_tiles;
-                const double ratio = (double)(mx + 2) * (my + 2) * (mz + 2) / ((double)mx * my * mz);
-                // a block that breaks the limits is taken only while nothing fits
-                const double score = ok ? ratio : 1e200 + ratio;
-                if (score < best_ratio - 1e-9 ||
-                    (fabs(score - best_ratio) <= 1e-9 && mx > best[0])) {
-                    best_ratio = score;
+                                home <= home_max;
+                // a block that breaks the limits is taken only while nothing fits,
+                // the fewest staged cells first
+                const double score =
+                    ok ? tiling_cost(k, tiles, home, staged, c->alone) : 1e200 * cells;
+                if (score < best_score * (1.0 - 1e-9) ||
+                    (score <= best_score * (1.0 + 1e-9) && mx > best[0])) {
+                    best_score = score;
                     best[0] = ax;
                     best[1] = ay;
                     best[2] = az;
@@ -136,7 +162,7 @@ static void plan_tiles(md_ctx* c)
         // few tiles, which leave room on the CUs: a wave per home cell of a tile of
         // 12 (100 003 LJ atoms, 486 tiles: 60 against 76 us; 2.048M, 8640 tiles:
         // 723 against 668 us, as two such workgroups share a CU instead of three)
-        waves = home_cells >= 12 && c->min_tiles > 0 && k.n_tiles < 3 * 256
+        waves = home_cells >= 12 && c->alone && k.n_tiles < 3 * 256
                     ? 12
                     : (home_cells >= 8 ? 8 : (home_cells >= 4 ? 4 : home_cells));
     }

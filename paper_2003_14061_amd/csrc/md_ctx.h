@@ -23,7 +23,7 @@ enum Region {
 }  // namespace md
 
 struct md_ctx;
-void replan_tiles(md_ctx* c);  // the tiling again, after a change of min_tiles
+void replan_tiles(md_ctx* c);  // the tiling again, after a change of `alone`
 
 // Tuning cache (md_tune.hip): keys of a system or a batch with a candidate
 // list on this device, and the cached tuning of a key in a cache file.
@@ -56,7 +56,7 @@ struct md_ctx {
     int tile_cells = 0, tile_y = 0, tile_z = 0;  // requested block size (0: automatic)
     int tile_cells_res = 0, tile_y_res = 0, tile_z_res = 0;  // largest block in use
     int stage_cap = 0;              // requested staged-atom capacity (0: from density)
-    int min_tiles = 256;            // automatic tiling: at least this many tiles (one per CU)
+    bool alone = true;              // the system has the machine to itself (plan_tiles)
     // md_step's graph of kGraphSteps steps (see md_api.hip)
     bool graph_on = false;  // set by md_init from the system size
     hipGraph_t graph = nullptr;
