@@ -330,6 +330,16 @@ __device__ __forceinline__ bool last_block(DevState* dev, int n_wg)
     return last;
 }
 
+// The bonded terms' map from permanent id to slot: atom id is in slot k.  Ids
+// outside [0, n) are flagged.
+__device__ __forceinline__ void bond_slot(const KParams& p, int id, int k)
+{
+    if (id >= 0 && id < p.n)
+        p.slot_of[id] = k;
+    else
+        atomicOr(&p.dev->flags, (int)MD_FLAG_TOPOLOGY);
+}
+
 // Slot of atom i inside its cell c (every lane of the wave calls it; act:
 // lane i holds an atom).  Atoms stored in cell order put a wave's lanes into
 // runs of one cell: the first lane of each run takes one atomic for the whole
