@@ -584,7 +584,8 @@ static void cells_any(const KParams& k, int flags, hipStream_t s)
         if (force) launch_allpairs_fold(k, s);  // in a step the drift folds
     } else
         launch_cells(k, flags, s);
-    if (k.bonded_on) launch_bond_map(k, force, s);  // after any permutation of the slots
+    // after any permutation of the slots that has not done it
+    if (k.bonded_on && !(flags & kFoldCopy)) launch_bond_map(k, force, s);
 }
 
 static void neighbors_any(const KParams& k, int force, hipStream_t s)
@@ -755,15 +756,18 @@ static md_status step_launches(md_ctx* c, hipStream_t s, bool first, int32_t n,
     const bool tiled = k.pipeline == MD_PIPE_TILED;
     // the reorder's copy-back folded into the pass after the cell build (the
     // list build, or the cells-only force pass)
-    const int fold = tiled && k.reorder && !k.bonded_on ? kFoldCopy : 0;
+    const int fold = tiled && k.reorder && (nl || !k.bonded_on) ? kFoldCopy : 0;
     // cells only: the cells are rebuilt every step, so the integration pass
     // bins the atoms and a small system sorts them in one workgroup
     const bool cells = tiled && !nl;
     const int cflags = fold | (cells ? kFoldBin | kSortSmallOk : 0);
     const int fflags = cells ? fold : 0;
-    // the finish with the cell build behind it (one launch for a small system)
+    // the finish with the cell build behind it (one launch for a small system);
+    // a bonded system's map of slots goes with the folded sort only
+    const bool joined = tiled && (!k.bonded_on || fold);
+    const bool slots = joined && finish_bins(k, cflags);
     auto finish_and_cells = [&](int phase) {
-        if (tiled && !k.bonded_on) {
+        if (joined) {
             launch_finish_cells(k, cflags, phase, record_every, false, s);
         } else {
             launch_integrate_finish(k, phase, record_every, s);
@@ -773,7 +777,7 @@ static md_status step_launches(md_ctx* c, hipStream_t s, bool first, int32_t n,
     if (s != c->stream) {  // captured into a graph: never timed, never reordered
         for (int32_t i = 0; i < n; ++i) {
             const int phase = first && i == 0 ? 0 : 1;
-            launch_integrate_pass(k, phase, s, cells);
+            launch_integrate_pass(k, phase, s, cells, false, slots && phase == 1);
             finish_and_cells(phase);
             if (nl) neighbors_any(k, fold, s);
             forces_any(k, s, fflags);
@@ -782,10 +786,12 @@ static md_status step_launches(md_ctx* c, hipStream_t s, bool first, int32_t n,
     }
     for (int32_t i = 0; i < n; ++i) {
         const int phase = first && i == 0 ? 0 : 1;
-        timed(c, MD_PART_INTEGRATE,
-              [&] { launch_integrate_pass(k, phase, s, cells); });
         const bool reorder = layer_reorder_on(c) && (step0 + i + 1) % k.reorder == 0;
-        if (!c->timing && !reorder) {
+        const bool together = !c->timing && !reorder;
+        timed(c, MD_PART_INTEGRATE, [&] {
+            launch_integrate_pass(k, phase, s, cells, false, slots && together && phase == 1);
+        });
+        if (together) {
             finish_and_cells(phase);
         } else if (cells && k.n <= kSortSmall && !k.bonded_on) {
             // the finish and the cell build in one launch (counted as cells)

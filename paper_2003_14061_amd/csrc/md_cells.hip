@@ -85,19 +85,21 @@ __global__ void k_bin(B b, int force)
     bin_atoms(p, wg);
 }
 
-// k_bin behind a fused force pass, with the finish of that pass: every
-// workgroup takes the rebuild decision itself from the sixteen displacement
-// maxima (one load), the first one also counts and records the step
-// (finish_step, which leaves the maxima for the others; the scan after it
-// clears them).  Saves the finish's launch, 4.3 us of a 42 us step at 256 000 atoms.
-__global__ __launch_bounds__(1024) void k_bin_finish(Single b, int record_every)
+// k_bin with the finish of the integration pass (or fused force pass) before it:
+// every workgroup takes the rebuild decision itself from the sixteen displacement
+// maxima (one load), the first one also counts and records the step (finish_step,
+// which leaves the maxima for the others; the scan after it clears them).  Saves
+// the finish's launch, 4.3 us of a 42 us step at 256 000 WCA atoms, 3.6 of 70 at the
+// melt of 262 144.  Not over replicas: there every workgroup would read its
+// replica's parameters first, 8.6 us against 4.8 + 5.2 apart and no faster a step.
+__global__ __launch_bounds__(1024) void k_bin_finish(Single b, int record_every, int fused)
 {
     const KParams& p = b.p;
     const Wg wg{(int)blockIdx.x, (int)gridDim.x};
     bool rebuild;
     if (wg.id == 0) {
         __shared__ double red[(1024 / kWave) * 5];
-        rebuild = finish_step(p, 1, record_every, true, red, false);
+        rebuild = finish_step<true>(p, 1, record_every, fused != 0, red);
     } else {
         __shared__ int rb;
         if (threadIdx.x < kWave) {
@@ -359,6 +361,7 @@ __device__ __forceinline__ void sort_slot(const KParams& p, int q)
         }
         p.sid[d] = key;
         p.scell[d] = c;
+        if (kPermute == P_STATE && p.bonded_on) bond_slot(p, key, d);
     }
 }
 
@@ -618,6 +621,7 @@ __global__ __launch_bounds__(kScanThreads) void k_cells_lds(Single b, SmallCells
                     p.svy[d[u]] = v[u][4];
                     p.svz[d[u]] = v[u][5];
                     p.sid[d[u]] = key[u];
+                    if (p.bonded_on) bond_slot(p, key[u], d[u]);
                     p.scell[d[u]] = cell[u];
                 }
             }
@@ -765,6 +769,12 @@ void launch_cell_scan(const KParams& p, hipStream_t s)
     hipLaunchKernelGGL(k_scan<Single>, dim3(1), dim3(kScanThreads), 0, s, Single{p}, 1);
 }
 
+bool finish_bins(const KParams& p, int flags)
+{
+    return p.mode == MD_NEIGHBOR_LIST &&
+           !(cells_lds_bytes(p) && (!p.reorder || (flags & kFoldCopy)));
+}
+
 void launch_finish_cells(const KParams& p, int flags, int phase, int record_every, bool fused,
                          hipStream_t s)
 {
@@ -784,10 +794,10 @@ void launch_finish_cells(const KParams& p, int flags, int phase, int record_ever
                                phase, record_every, fused ? 1 : 0);
         return;
     }
-    if (fused && phase == 1 && p.mode == MD_NEIGHBOR_LIST) {
+    if (phase == 1 && finish_bins(p, flags)) {
         const int t = p.block > kFinishThreads ? p.block : kFinishThreads;
         hipLaunchKernelGGL(k_bin_finish, dim3(grid_of(p, G_ATOMS)), dim3(t), 0, s, Single{p},
-                           record_every);
+                           record_every, fused ? 1 : 0);
         launch_cells(p, flags | kBinDone, s);
         return;
     }

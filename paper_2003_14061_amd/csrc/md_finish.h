@@ -93,7 +93,7 @@ __device__ __forceinline__ void record_step(const KParams& p, int n_wg, int reco
     }
 }
 
-// The largest squared displacement of a fused force pass (in every lane; a whole
+// The largest of the displacement maxima in dev->dmax_slot (in every lane; a whole
 // wave calls it).
 __device__ __forceinline__ double step_dmax2(const KParams& p)
 {
@@ -105,12 +105,14 @@ __device__ __forceinline__ double step_dmax2(const KParams& p)
 
 // The end of an integration pass: count the step and record it (phase >= 1),
 // and from the largest displacement decide whether the cells and list are
-// rebuilt before the next force pass (phase <= 1; returned in every thread).  By one workgroup of at
-// least kFinishThreads threads (red: LDS, (blockDim / 64) * 5 doubles).  fused:
-// the pass was a fused force pass (launch_forces_step), whose displacement maxima
-// are then cleared for the next one unless `clear` is false.
+// rebuilt before the next force pass (phase <= 1; returned in every thread).  By one
+// workgroup of at least kFinishThreads threads (red: LDS, (blockDim / 64) * 5
+// doubles).  fused: the pass was a fused force pass (launch_forces_step).
+// kSlots: its displacement maxima are in dev->dmax_slot in any case, and a later
+// kernel clears them (k_bin_finish); else a fused pass's are cleared here.
+template <bool kSlots = false>
 __device__ __forceinline__ bool finish_step(const KParams& p, int phase, int record_every,
-                                            bool fused, double* red, bool clear = true)
+                                            bool fused, double* red)
 {
     bool rebuild = false;
     const int n_wg = grid_of(p, G_INTEGRATE);
@@ -118,10 +120,10 @@ __device__ __forceinline__ bool finish_step(const KParams& p, int phase, int rec
     if (phase <= 1) {
         __shared__ int rb_all;
         double m = 0.0;
-        if (fused) {
+        if (kSlots || fused) {
             if (threadIdx.x < kWave) {
                 m = step_dmax2(p);
-                if (clear && threadIdx.x < kDmaxSlots) p.dev->dmax_slot[threadIdx.x] = 0;
+                if (!kSlots && threadIdx.x < kDmaxSlots) p.dev->dmax_slot[threadIdx.x] = 0;
             }
         } else {
             m = finish_max<kFinishThreads>(p.ipart, n_wg, 8, 4, red);

@@ -30,9 +30,10 @@ namespace md {
 
 // kBin (cells-only steps, which rebuild the cells every step): the drift also
 // folds the positions into [0, L) and bins them (cell and slot, as k_bin), so
-// that the cell build that follows starts at the scan.
+// that the cell build that follows starts at the scan.  slots: the largest
+// displacement goes to dev->dmax_slot as well (a k_bin_finish follows).
 template <typename F, class B, bool kBin>
-__global__ __launch_bounds__(kIntThreads) void k_integrate(B b, int phase, int to_scratch)
+__global__ __launch_bounds__(kIntThreads) void k_integrate(B b, int phase, int to_scratch, int slots)
 {
     Wg wg;
     KParams p;
@@ -128,6 +129,9 @@ __global__ __launch_bounds__(kIntThreads) void k_integrate(B b, int phase, int t
         o[2] = acc[2];
         o[3] = acc[3];
         o[4] = dmax2;
+        if (slots)
+            atomicMax(&p.dev->dmax_slot[wg.id % kDmaxSlots],
+                      (unsigned long long)__double_as_longlong(dmax2));
     }
 }
 
@@ -185,19 +189,19 @@ __global__ __launch_bounds__(kIntThreads) void k_observe(KParams p)
 
 template <class B>
 static void integrate_pass(const B& b, const LaunchShape& sh, int phase, hipStream_t s, bool bin,
-                           bool to_scratch)
+                           bool to_scratch, bool slots = false)
 {
     const dim3 g(sh.grid[G_INTEGRATE]), t(kIntThreads);
-    const int out = to_scratch ? 1 : 0;
+    const int out = to_scratch ? 1 : 0, ds = slots ? 1 : 0;
     if (bin && phase <= 1) {
         if (sh.precision == MD_FP64)
-            hipLaunchKernelGGL((k_integrate<double, B, true>), g, t, 0, s, b, phase, out);
+            hipLaunchKernelGGL((k_integrate<double, B, true>), g, t, 0, s, b, phase, out, ds);
         else
-            hipLaunchKernelGGL((k_integrate<float, B, true>), g, t, 0, s, b, phase, out);
+            hipLaunchKernelGGL((k_integrate<float, B, true>), g, t, 0, s, b, phase, out, ds);
     } else if (sh.precision == MD_FP64) {
-        hipLaunchKernelGGL((k_integrate<double, B, false>), g, t, 0, s, b, phase, out);
+        hipLaunchKernelGGL((k_integrate<double, B, false>), g, t, 0, s, b, phase, out, ds);
     } else {
-        hipLaunchKernelGGL((k_integrate<float, B, false>), g, t, 0, s, b, phase, out);
+        hipLaunchKernelGGL((k_integrate<float, B, false>), g, t, 0, s, b, phase, out, ds);
     }
 }
 
@@ -222,9 +226,10 @@ void launch_integrate(const KParams& p, int phase, int record_every, hipStream_t
     integrate_seq(Single{p}, shape_of(p), phase, record_every, s);
 }
 
-void launch_integrate_pass(const KParams& p, int phase, hipStream_t s, bool bin, bool to_scratch)
+void launch_integrate_pass(const KParams& p, int phase, hipStream_t s, bool bin, bool to_scratch,
+                           bool slots)
 {
-    integrate_pass(Single{p}, shape_of(p), phase, s, bin, to_scratch);
+    integrate_pass(Single{p}, shape_of(p), phase, s, bin, to_scratch, slots);
 }
 
 void launch_integrate_finish(const KParams& p, int phase, int record_every, hipStream_t s,

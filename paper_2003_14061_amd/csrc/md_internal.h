@@ -354,6 +354,10 @@ void launch_layer_export(const KParams& p, int32_t* out, hipStream_t s);
 void launch_layer_reorder(const KParams& p, hipStream_t s);
 void launch_cell_scan(const KParams& p, hipStream_t s);
 // launch_integrate_finish, then launch_cells(flags): one launch for a small system.
+// finish_bins: else, in phase 1, the finish goes with the binning (k_bin_finish), so
+// the pass before leaves its displacement maxima in dev->dmax_slot (a fused force
+// pass does; launch_integrate_pass with slots).
+bool finish_bins(const KParams& p, int flags);
 void launch_finish_cells(const KParams& p, int flags, int phase, int record_every, bool fused,
                          hipStream_t s);
 int allpairs_home_blocks(int n);
@@ -371,7 +375,7 @@ void launch_clear(const KParams& p, hipStream_t s);
 // build copies each tile's home atoms into the state arrays (saving the
 // separate copy-back pass and its launch).  The forces are left out of that
 // permutation: the force pass that follows in every such sequence writes them
-// anew.
+// anew.  The sort then also writes the bonded terms' map of slots.
 constexpr int kFoldCopy = 2;
 // Further launch_cells flags of md_step's cells-only sequence: kFoldBin --
 // the integration pass has already binned the atoms (k_bin is left out);
@@ -408,9 +412,10 @@ void launch_integrate(const KParams& p, int phase, int record_every, hipStream_t
 // The two halves of launch_integrate: the per-atom pass, then the per-system
 // finish (reductions, step count and record, rebuild decision).
 // bin: the pass also bins the atoms (cells-only steps; with phase <= 1 only).
-// to_scratch: the drifted positions go to the scratch arrays.
+// to_scratch: the drifted positions go to the scratch arrays.  slots: see
+// finish_bins.
 void launch_integrate_pass(const KParams& p, int phase, hipStream_t s, bool bin = false,
-                           bool to_scratch = false);
+                           bool to_scratch = false, bool slots = false);
 // fused: the pass was a fused force pass (its partials, see launch_forces_step)
 void launch_integrate_finish(const KParams& p, int phase, int record_every, hipStream_t s,
                              bool fused = false);
