@@ -524,13 +524,24 @@ __device__ __forceinline__ int home_column_cell(const Stage& s, int t1, int e)
     return t1 + lo;
 }
 
+// Wrap bits of staged entry e of a run of three cells, the second and third from
+// entries b1 and b2 on.
+__device__ __forceinline__ int run_flag(int e, int b1, int b2, int fl0, int fl1, int fl2)
+{
+    return e < b1 ? fl0 : (e < b2 ? fl1 : fl2);
+}
+
 // The list of home atom h, by one lane.  Returns the number of entries found
 // (beyond the capacity: overflow).
 //
-// Bound by instruction issue: nearly every candidate is a hit of some lane of the
-// wave, so the code of a hit counts as much as the test.  A hit shifts its entry
-// into the top of the chunk (two instructions); count and capacity are looked at
-// where a chunk is full.  Two candidates are read at a time.
+// Bound by instruction issue.  With the candidates in LDS a window's are tested
+// first, four at a time, one bit each of a mask (eight instructions a candidate and
+// no branch); then the set bits are taken in order, as many rounds as the fullest
+// lane has hits.  (A branch per candidate to the code of a hit runs that code for
+// nearly every candidate, since some lane of the wave hits: builds of 64 replicas
+// 194 us so and 163 with masks, of 262 144 melt atoms 45 and 42, of 256 000 WCA atoms
+// 42.5 and 41.5.)  A hit shifts its entry into the top of the chunk; count and
+// capacity are looked at where a chunk is full.
 template <int kImage, bool kFits, bool kHalf>
 __device__ __forceinline__ int nl_home_atom(const KParams& p, const Stage& s, int h)
 {
@@ -560,57 +571,68 @@ __device__ __forceinline__ int nl_home_atom(const KParams& p, const Stage& s, in
             col += p.npad;
         }
     };
-    // Staged as periodic images (kShifted, see stage_atoms), or with no wrapped cell
-    // in the tile, the three cells of a window are one run of staged atoms whose raw
-    // separation is the minimum image; a shifted partner's differs from that of the
-    // wrap bits by roundings, so a pair within those of the list radius is decided by
-    // the wrap bits.
-    constexpr bool kShifted = kImage == 1 && kFits && !kHalf;
-    constexpr int kRuns = kImage == 0 || kShifted ? 1 : 3;
-    const double reach2 = kShifted ? p.box_reach2 : p.rl2;
     for (int sg = 0; sg < 9; ++sg) {
         const int tw = window_cell(s, home_t, sg);
+        if constexpr (kFits && !kHalf) {
+            // The three cells of a window are one run of staged atoms.  In a tile with
+            // no wrapped cell, or staged as periodic images (kShifted, see
+            // stage_atoms), the raw separation is the minimum image; a shifted
+            // partner's differs from that of the wrap bits by roundings, so a pair
+            // within those of the list radius is decided by the wrap bits.
+            constexpr bool kShifted = kImage == 1;
+            const double reach2 = kShifted ? p.box_reach2 : p.rl2;
+            const int eb = s.off[tw], ee = s.off[tw + 3];
+            int b1 = 0, b2 = 0, fl0 = 0, fl1 = 0, fl2 = 0;
+            if (kImage != 0) {
+                b1 = s.off[tw + 1];
+                b2 = s.off[tw + 2];
+                fl0 = s.flag[tw];
+                fl1 = s.flag[tw + 1];
+                fl2 = s.flag[tw + 2];
+            }
+            for (int e0 = eb; e0 < ee; e0 += 32) {
+                const int n = ee - e0 < 32 ? ee - e0 : 32;
+                uint32_t in = 0, sure = 0;
+                for (int k = 0; k < n; k += 4) {
+                    // past the run: up to three entries of other cells or of the
+                    // tables behind the staged atoms, masked below
+                    uint32_t in4 = 0, sure4 = 0;
 #pragma unroll
-        for (int w = 0; w < kRuns; ++w) {
-            const int t = tw + w;
-            const int eb = s.off[t], ee = s.off[t + (kRuns == 1 ? 3 : 1)];
-            const int fl = kImage == 0 ? 0 : s.flag[t];
-            if constexpr (kFits && !kHalf) {
-                int b1 = 0, b2 = 0, fl1 = 0, fl2 = 0;
-                if (kShifted) {
-                    b1 = s.off[t + 1];
-                    b2 = s.off[t + 2];
-                    fl1 = s.flag[t + 1];
-                    fl2 = s.flag[t + 2];
-                }
-                for (int e0 = eb; e0 < ee; e0 += 2) {
-                    double r2[2];
-#pragma unroll
-                    for (int u = 0; u < 2; ++u) {
+                    for (int u = 3; u >= 0; --u) {
                         double xj, yj, zj;
-                        lds_xyz(s.p3, e0 + u, xj, yj, zj);  // at most the sentinel's
+                        lds_xyz(s.p3, e0 + k + u, xj, yj, zj);
                         double dx = xi - xj, dy = yi - yj, dz = zi - zj;
-                        image<kShifted ? 0 : kImage>(p, fl, dx, dy, dz);
-                        r2[u] = dist2(dx, dy, dz);
+                        image<kShifted ? 0 : kImage>(p, 0, dx, dy, dz);
+                        const double r2 = dist2(dx, dy, dz);
+                        in4 = in4 + in4 + (r2 < reach2 ? 1u : 0u);
+                        if (kShifted) sure4 = sure4 + sure4 + (r2 < p.rl2_in ? 1u : 0u);
                     }
-#pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        const int e = e0 + u;
-                        bool in = r2[u] < reach2 && e != e_self && (u == 0 || e < ee);
-                        if (in) {
-                            const int f = !kShifted || e < b1 ? fl : (e < b2 ? fl1 : fl2);
-                            if (kShifted && r2[u] > p.rl2_in) {
-                                const int j = staged_slot(p, s, e);
-                                double dx = xi - p.x[j], dy = yi - p.y[j], dz = zi - p.z[j];
-                                image<1>(p, f, dx, dy, dz);
-                                in = dist2(dx, dy, dz) < p.rl2;
-                            }
-                            if (in) hit(e, f);
-                        }
+                    in |= in4 << k;
+                    sure |= sure4 << k;
+                }
+                in &= 0xffffffffu >> (32 - n);
+                if (sg == 4 && (uint32_t)(e_self - e0) < 32u) in &= ~(1u << (e_self - e0));
+                if (kShifted) {
+                    for (uint32_t edge = in & ~sure; edge != 0; edge &= edge - 1) {
+                        const int e = e0 + __builtin_ctz(edge);
+                        const int j = staged_slot(p, s, e);
+                        double dx = xi - p.x[j], dy = yi - p.y[j], dz = zi - p.z[j];
+                        image<1>(p, run_flag(e, b1, b2, fl0, fl1, fl2), dx, dy, dz);
+                        if (!(dist2(dx, dy, dz) < p.rl2)) in &= ~(edge & -edge);
                     }
                 }
-            } else {
-                const int tslot = s.slot[t];
+                for (; in != 0; in &= in - 1) {
+                    const int e = e0 + __builtin_ctz(in);
+                    hit(e, kImage == 0 ? 0 : run_flag(e, b1, b2, fl0, fl1, fl2));
+                }
+            }
+        } else {
+            constexpr int kRuns = kImage == 0 ? 1 : 3;
+#pragma unroll
+            for (int w = 0; w < kRuns; ++w) {
+                const int t = tw + w;
+                const int eb = s.off[t], ee = s.off[t + (kRuns == 1 ? 3 : 1)];
+                const int fl = kImage == 0 ? 0 : s.flag[t], tslot = s.slot[t];
                 if (kHalf && tslot + (ee - eb) <= pos_i) continue;
                 for (int e = eb; e < ee; ++e) {
                     double xj, yj, zj;
