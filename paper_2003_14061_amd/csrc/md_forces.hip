@@ -397,9 +397,13 @@ __global__ __attribute__((amdgpu_waves_per_eu(6))) void k_forces_tiles(B b)
 // and the force pass by VALU issue, so together the integration's traffic,
 // less the forces and the reread positions (96 B per atom), hides under the pair
 // walk: 238 us against 223 + 47 us at 2.048M LJ atoms, 19.3 against 16.5 + 8.4 us
-// at 256 000 WCA atoms, 69 against 56 + 25 us for 64 replicas.  Energies, virial and kinetic sums only when the history
-// asks for the step (DevState::record, set by the finish before this launch);
-// the largest displacement always.
+// at 256 000 WCA atoms, 69 against 56 + 25 us for 64 replicas (the latter two 18.2
+// and 66.5 us with the tile shapes of tiling_cost).  Velocities and references
+// loaded ahead of the walk, one triple per lane of a group, measured no gain (18.2
+// -> 18.7 us, 66.5 -> 65.2, 246 -> 249 at 2.048M): the other waves hide those loads.
+// Energies, virial and kinetic sums only when the history asks for the step
+// (DevState::record, set by the finish before this launch); the largest
+// displacement always.
 template <typename F, int LANES, class B>
 __global__ __attribute__((amdgpu_waves_per_eu(6))) void k_forces_step(B b)
 {
