@@ -167,6 +167,18 @@ static void plan_tiles(md_ctx* c)
                     : (home_cells >= 8 ? 8 : (home_cells >= 4 ? 4 : home_cells));
     }
     waves = waves < 1 ? 1 : waves;
+    // up to three tiles per CU of few home cells: up to four waves per cell, each
+    // with a part of its atoms, as many as the CU holds (builds: 4000 LJ atoms, 125
+    // tiles of one cell, 60 -> 22 us; 20 000, 250 of 4, 44 -> 28; 32 000 FP32, 216 of
+    // 8, 62 -> 39; 50 000, 507 of 5, 66 -> 43, and 59 at 16 waves; 70 000, 512 of 8,
+    // 53 at 8 and 64 at 16)
+    if (c->nl_block_req <= 0 && c->alone && k.n_tiles <= 3 * 256) {
+        const int room = k.n_tiles <= 256 ? 16 : (k.n_tiles <= 2 * 256 ? 12 : 8);
+        const int parts = room / home_cells < 4 ? room / home_cells : 4;
+        if (parts > 1 &&
+            nl_queue_fits(k, k.nl_method, kWave * home_cells * parts, c->lds_limit))
+            waves = home_cells * parts;
+    }
     const int nlb = c->nl_block_req > 0 ? c->nl_block_req : kWave * waves;
     k.nl_block = nlb < kWave ? kWave : (nlb > 1024 ? 1024 : nlb);
     k.nl_queue = nl_queue_fits(k, k.nl_method, k.nl_block, c->lds_limit);

@@ -309,17 +309,24 @@ __device__ __forceinline__ void near_image(const KParams& p, int fl, double bx, 
     if (fl & 4) cz += bz > cz ? p.L : -p.L;
 }
 
-// The lists of home cell hc's atoms (see above).  q: this wave's LDS: the queue
-// and, once a block's candidates are in registers, one list in its place.
-// small, wmax as nl_home_cell.
+// The lists of the atoms of home cell hc, of them part i of split near-equal ones (see
+// above).  q: this wave's LDS: the queue and, once a block's candidates
+// are in registers, one list in its place.  small, wmax as nl_home_cell.
 template <int kImage, bool kFull>
-__device__ __forceinline__ void nl_home_cell_q(const KParams& p, const Stage& s, int hc,
-                                               bool small, MD_LDS uint16_t* q, int& wmax)
+__device__ __forceinline__ void nl_home_cell_q(const KParams& p, const Stage& s, int hc, int i,
+                                               int split, bool small, MD_LDS uint16_t* q,
+                                               int& wmax)
 {
     const int lane = cell_lane();
     const int home_t = home_cell(s, hc);
-    const int hb = uniform(s.off[home_t]), he = uniform(s.off[home_t + 1]);
-    const int hslot0 = uniform(s.slot[home_t]);
+    int hb = uniform(s.off[home_t]), he = uniform(s.off[home_t + 1]);
+    int hslot0 = uniform(s.slot[home_t]);
+    if (split > 1) {
+        const int n = he - hb, first = uniform(n * i / split);
+        he = hb + uniform(n * (i + 1) / split);
+        hb += first;
+        hslot0 += first;
+    }
     MD_LDS uint64_t* const q64 = (MD_LDS uint64_t*)q;
     const uint32_t cap = (uint32_t)p.cap;  // a multiple of 4
     const uint32_t rowb = 8u * (uint32_t)p.npad;
@@ -747,7 +754,11 @@ __device__ __forceinline__ void nl_tile(const KParams& p, int t, char* smem, int
     // round of 64 candidates at a time: those paths then hold fewer registers
     // than the common ones (the kernel's register count is that of its largest
     // path), which keeps six waves per SIMD.
-    for (int hc = wid; hc < ncells; hc += nw) {
+    // More waves than home cells: the cells' atoms are split among them (few tiles,
+    // whose waves would leave the CUs idle; see plan_tiles).
+    const int split = p.nl_queue && s.fits && mode != 2 && nw > ncells ? nw / ncells : 1;
+    for (int u = wid; u < ncells * split; u += nw) {
+        const int hc = split > 1 ? uniform(u / split) : u, part = u - hc * split;
         if (kFull && mode == 2) {
             if (s.fits)
                 nl_home_cell<2, kHalf, true, 1, kFull>(p, s, hc, small, wmax);
@@ -759,7 +770,7 @@ __device__ __forceinline__ void nl_tile(const KParams& p, int t, char* smem, int
             if constexpr (kHalf) {
                 nl_home_cell<0, kHalf, true, kNlRounds, kFull>(p, s, hc, small, wmax);
             } else if (p.nl_queue) {
-                nl_home_cell_q<0, kFull>(p, s, hc, small, queue, wmax);
+                nl_home_cell_q<0, kFull>(p, s, hc, part, split, small, queue, wmax);
             } else {
                 nl_home_cell<0, kHalf, true, 1, kFull>(p, s, hc, small, wmax);
             }
@@ -767,7 +778,7 @@ __device__ __forceinline__ void nl_tile(const KParams& p, int t, char* smem, int
             if constexpr (kHalf) {
                 nl_home_cell<1, kHalf, true, kNlRounds, kFull>(p, s, hc, small, wmax);
             } else if (p.nl_queue) {
-                nl_home_cell_q<1, kFull>(p, s, hc, small, queue, wmax);
+                nl_home_cell_q<1, kFull>(p, s, hc, part, split, small, queue, wmax);
             } else {
                 nl_home_cell<1, kHalf, true, 1, kFull>(p, s, hc, small, wmax);
             }
