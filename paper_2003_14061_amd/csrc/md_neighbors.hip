@@ -263,7 +263,8 @@ __device__ __forceinline__ void nl_home_cell(const KParams& p, const Stage& s, i
 // vector and 156 M scalar instructions in the earlier build, which tested all
 // 533 candidates and stored entry by entry).  Forced builds: 830 -> 668 us at
 // 2.048M LJ atoms, 91 -> 60 us at 100 003, 93 -> 70 us at 32 000, 38 -> 32 us at
-// 10 007.  Storing eight lists together, a row of their chunks as one run of 64
+// 10 007 (the latter two 39 and 21 us with each cell's atoms shared by several
+// waves, see plan_tiles).  Storing eight lists together, a row of their chunks as one run of 64
 // bytes, took an eighth of the write requests and was slower (817 us): requests
 // do not bound it.
 
