@@ -320,41 +320,17 @@ __device__ __forceinline__ double gr_norm(const KParams& p, const GrArgs& g, int
 // Bins whose kernel reaches distance r: |r - r_b| < 3w.
 __device__ __forceinline__ void bin_range(const GrArgs& g, double r, int& b0, int& b1)
 {
-    b0 = (int)floor((r - 3.0 * g.width) * g.inv_delta - 0.5);
-    b1 = (int)ceil((r + 3.0 * g.width) * g.inv_delta - 0.5);
+    const double delta = g.rmax / g.n_bins;
+    b0 = (int)floor((r - 3.0 * g.width) / delta - 0.5);
+    b1 = (int)ceil((r + 3.0 * g.width) / delta - 0.5);
     b0 = b0 < 0 ? 0 : b0;
     b1 = b1 > g.n_bins - 1 ? g.n_bins - 1 : b1;
 }
 
-// The Gaussian exp(-t^2 / 2 w^2) at the bins of a pair in turn, t falling by one
-// bin width each: from one bin to the next it grows by a factor that itself
-// shrinks by a constant one, so a pair takes two exponentials instead of one per
-// bin (seven at a width of one bin).  Bins far wider than the kernel, where the
-// factor could overflow, take an exponential each.
-struct GrGauss {
-    double t, e, f;
-    __device__ __forceinline__ GrGauss(const GrArgs& g, double r, int b)
-    {
-        t = r - (b + 0.5) * g.delta;
-        at(g);
-        f = exp((t - 0.5 * g.delta) * g.delta * g.inv_w * g.inv_w);
-    }
-    __device__ __forceinline__ void at(const GrArgs& g)
-    {
-        e = exp(-0.5 * (t * g.inv_w) * (t * g.inv_w));
-    }
-    __device__ __forceinline__ void next(const GrArgs& g)
-    {
-        t -= g.delta;
-        if (g.chain) {
-            e *= f;
-            f *= g.fall;
-        } else {
-            at(g);
-        }
-    }
-};
-
+// An exponential for every bin a pair reaches.  (From one bin to the next by a factor
+// that itself shrinks took two per pair: the forward's and the gradient's kernel 65
+// and 60 us less at 32 000 atoms and 50 bins; but the roundings grow with the square
+// of the bins a pair reaches, to 1e-11 of the gradient at 1024 bins.)
 struct GrOp {
     const GrArgs& g;
     unsigned long long* lh;  // LDS histogram
@@ -362,16 +338,15 @@ struct GrOp {
     __device__ __forceinline__ void operator()(double, double, double, double r2, int, int)
     {
         if (!(r2 < reach2)) return;
-        const double r = sqrt(r2);
+        const double r = sqrt(r2), w = g.width;
         int b0, b1;
         bin_range(g, r, b0, b1);
-        GrGauss q(g, r, b0);
         for (int b = b0; b <= b1; ++b) {
-            if (fabs(q.t) < 3.0 * g.width) {
-                const double k = (q.e - g.edge) * g.norm;
+            const double t = r - bin_center(g, b);
+            if (fabs(t) < 3.0 * w) {
+                const double k = (exp(-0.5 * (t / w) * (t / w)) - exp(-4.5)) / (w * kSqrt2Pi);
                 atomicAdd(&lh[b], (unsigned long long)llrint(k * g.scale));
             }
-            q.next(g);
         }
     }
 };
@@ -432,16 +407,15 @@ struct GrGradOp {
                                                int)
     {
         if (!(r2 < reach2)) return;
-        const double r = sqrt(r2);
+        const double r = sqrt(r2), w = g.width;
         int b0, b1;
         bin_range(g, r, b0, b1);
         double c = 0.0;
-        GrGauss q(g, r, b0);
         for (int b = b0; b <= b1; ++b) {
-            if (fabs(q.t) < 3.0 * g.width) c -= wn[b] * (q.t * q.e);
-            q.next(g);
+            const double t = r - bin_center(g, b);
+            if (fabs(t) < 3.0 * w) c -= wn[b] * ((t / w) * exp(-0.5 * (t / w) * (t / w)));
         }
-        c *= g.norm * g.inv_w * g.inv_w;
+        c /= w * w * kSqrt2Pi;
         const double f = 2.0 * c / r;
         ax += f * dx;
         ay += f * dy;

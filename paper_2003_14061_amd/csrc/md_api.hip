@@ -1084,16 +1084,6 @@ static GrArgs gr_args(const md_ctx* c, const md_traj_params* tp, void* ws, const
     g.n_bins = tp->n_bins;
     g.rmax = tp->gr_rmax;
     g.width = tp->gr_width;
-    if (tp->n_bins > 0) {
-        const double dw = tp->gr_rmax / tp->n_bins / tp->gr_width;
-        g.delta = tp->gr_rmax / tp->n_bins;
-        g.inv_delta = tp->n_bins / tp->gr_rmax;
-        g.inv_w = 1.0 / tp->gr_width;
-        g.norm = 1.0 / (tp->gr_width * sqrt(2.0 * M_PI));
-        g.edge = exp(-4.5);
-        g.fall = exp(-dw * dw);
-        g.chain = dw <= 4.0;  // factors below exp(4 (3 + 4)), values above exp(-25)
-    }
     // fixed-point units: the largest possible bin sum (every atom, a full
     // list, each pair at the kernel's peak) stays below 2^62
     const double kmax = 1.0 / (tp->gr_width * sqrt(2.0 * M_PI));

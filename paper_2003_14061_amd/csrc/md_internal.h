@@ -129,10 +129,6 @@ struct GrArgs {
     double *ly, *lz;
     int32_t n_bins;
     double rmax, width, scale;  // scale: fixed-point units per unit of kernel value
-    double delta, inv_delta, inv_w, norm;  // bin width and its inverse, 1 / width, 1 / (width
-                                           // sqrt(2 pi))
-    double edge, fall;  // exp(-9/2), the kernel's value at 3 widths; exp(-(delta / width)^2)
-    int32_t chain;      // successive bins by factors (GrGauss)
 };
 
 // ---- where a workgroup's parameters come from ----
