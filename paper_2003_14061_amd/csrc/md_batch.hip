@@ -126,14 +126,13 @@ md_status upload(md_batch* b)
     }
     if (p0.mode == MD_NEIGHBOR_LIST) {
         // the method and the widest workgroup are the launch's, whatever a
-        // replica alone would take; queues only if every replica has room
-        int queue = 1;
-        for (int r = 0; r < R; ++r)
-            queue &= nl_queue_fits(kp[r], sh.nl_method, sh.nl_block, b->rep[r]->lds_limit);
+        // replica alone would take; queues for the replicas that have room
         for (int r = 0; r < R; ++r) {
             kp[r].nl_method = sh.nl_method;
             kp[r].nl_block = sh.nl_block;
-            kp[r].nl_queue = queue;
+            kp[r].nl_queue =
+                nl_queue_fits(kp[r], sh.nl_method, sh.nl_block, b->rep[r]->lds_limit);
+            sh.nl_queue |= kp[r].nl_queue;
             const size_t a = nl_lds_bytes(kp[r]), f = force_lds_bytes(kp[r]);
             sh.nl_lds = a > sh.nl_lds ? a : sh.nl_lds;
             sh.force_lds = f > sh.force_lds ? f : sh.force_lds;

@@ -295,7 +295,7 @@ struct Batch {
 // Uniform launch shape: workgroups per grid rule, block sizes, dynamic LDS.
 struct LaunchShape {
     int grid[G_KINDS];
-    int block, force_block, force_lanes, nl_block, nl_method, newton3;
+    int block, force_block, force_lanes, nl_block, nl_method, nl_queue, newton3;
     size_t nl_lds, force_lds;
     int precision, reorder, mode;
     // the list build's full kernel: some system has fewer than 5 cells per side

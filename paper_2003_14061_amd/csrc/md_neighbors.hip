@@ -687,8 +687,9 @@ __device__ __forceinline__ void nl_lanes(const KParams& p, const Stage& s, int& 
 // image rule of grids under 5 cells per side (mode 2) and list stores beyond
 // 32-bit offsets are compiled in; a kernel without them serves only grids of 5
 // cells per side or more whose lists fit the buffer stores, and holds fewer
-// registers.
-template <int kMethod, bool kHalf, bool kCopy, bool kFull>
+// registers.  kQueue: the cell waves have their queues
+// (KParams::nl_queue; in a batch, those of some replica).
+template <int kMethod, bool kHalf, bool kCopy, bool kFull, bool kQueue>
 __device__ __forceinline__ void nl_tile(const KParams& p, int t, char* smem, int& wmax)
 {
     const Tile g = tile_of(p, t);
@@ -757,7 +758,8 @@ __device__ __forceinline__ void nl_tile(const KParams& p, int t, char* smem, int
     // path), which keeps six waves per SIMD.
     // More waves than home cells: the cells' atoms are split among them (few tiles,
     // whose waves would leave the CUs idle; see plan_tiles).
-    const int split = p.nl_queue && s.fits && mode != 2 && nw > ncells ? nw / ncells : 1;
+    const bool share = kQueue && p.nl_queue && s.fits && mode != 2 && nw > ncells;
+    const int split = share ? nw / ncells : 1;
     for (int u = wid; u < ncells * split; u += nw) {
         const int hc = split > 1 ? uniform(u / split) : u, part = u - hc * split;
         if (kFull && mode == 2) {
@@ -768,21 +770,19 @@ __device__ __forceinline__ void nl_tile(const KParams& p, int t, char* smem, int
         } else if (!s.fits) {
             nl_home_cell<1, kHalf, false, 1, kFull>(p, s, hc, small, wmax);
         } else if (mode == 0 || !home_wraps(p, g, hc)) {
-            if constexpr (kHalf) {
+            if constexpr (!kQueue)
                 nl_home_cell<0, kHalf, true, kNlRounds, kFull>(p, s, hc, small, wmax);
-            } else if (p.nl_queue) {
+            else if (p.nl_queue)
                 nl_home_cell_q<0, kFull>(p, s, hc, part, split, small, queue, wmax);
-            } else {
+            else  // a replica without room for them, beside others
                 nl_home_cell<0, kHalf, true, 1, kFull>(p, s, hc, small, wmax);
-            }
         } else {
-            if constexpr (kHalf) {
+            if constexpr (!kQueue)
                 nl_home_cell<1, kHalf, true, kNlRounds, kFull>(p, s, hc, small, wmax);
-            } else if (p.nl_queue) {
+            else if (p.nl_queue)
                 nl_home_cell_q<1, kFull>(p, s, hc, part, split, small, queue, wmax);
-            } else {
+            else  // a replica without room for them, beside others
                 nl_home_cell<1, kHalf, true, 1, kFull>(p, s, hc, small, wmax);
-            }
         }
     }
 }
@@ -793,7 +793,7 @@ __device__ __forceinline__ void nl_tile(const KParams& p, int t, char* smem, int
 // last wave of workgroups).
 // At most 80 VGPRs: six waves per SIMD, which the LDS of the dense LJ tiles
 // (three workgroups of eight waves per CU) allows.
-template <class B, int kMethod, bool kHalf, bool kCopy, bool kFull>
+template <class B, int kMethod, bool kHalf, bool kCopy, bool kFull, bool kQueue>
 __global__ __attribute__((amdgpu_waves_per_eu(6))) void k_nl_tiles(B b, int force)
 {
     Wg wg;
@@ -802,7 +802,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(6))) void k_nl_tiles(B b, int forc
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const KParams q = kCopy ? scratch_view(p) : p;
     int wmax = 0;
-    nl_tile<kMethod, kHalf, kCopy, kFull>(q, xcd_tile(wg.id, wg.n), smem, wmax);
+    nl_tile<kMethod, kHalf, kCopy, kFull, kQueue>(q, xcd_tile(wg.id, wg.n), smem, wmax);
     // the longest list: one global atomic per workgroup
     const int mmax = workgroup_max(wmax);
     if (threadIdx.x == 0 && mmax > 0) {
@@ -840,12 +840,20 @@ template <class B, bool kHalf, bool kCopy, bool kFull>
 static void neighbors_seq(const B& b, const LaunchShape& sh, int force, hipStream_t s)
 {
     const dim3 g(sh.grid[G_NL]), t(sh.nl_block);
-    if (sh.nl_method == MD_NL_CELL_WAVES)
-        hipLaunchKernelGGL((k_nl_tiles<B, MD_NL_CELL_WAVES, kHalf, kCopy, kFull>), g, t, sh.nl_lds,
-                           s, b, force);
-    else
-        hipLaunchKernelGGL((k_nl_tiles<B, MD_NL_LANES, kHalf, kCopy, kFull>), g, t, sh.nl_lds, s,
-                           b, force);
+    if (sh.nl_method != MD_NL_CELL_WAVES) {
+        hipLaunchKernelGGL((k_nl_tiles<B, MD_NL_LANES, kHalf, kCopy, kFull, false>), g, t,
+                           sh.nl_lds, s, b, force);
+        return;
+    }
+    if constexpr (!kHalf) {
+        if (sh.nl_queue) {
+            hipLaunchKernelGGL((k_nl_tiles<B, MD_NL_CELL_WAVES, kHalf, kCopy, kFull, true>), g, t,
+                               sh.nl_lds, s, b, force);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_nl_tiles<B, MD_NL_CELL_WAVES, kHalf, kCopy, kFull, false>), g, t,
+                       sh.nl_lds, s, b, force);
 }
 
 template <class B, bool kHalf, bool kCopy>
