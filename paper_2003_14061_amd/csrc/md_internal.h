@@ -54,6 +54,8 @@ struct KParams {
     double eps, sigma;
     double rl2_in, box_reach2;  // the list radius squared, less and more than the
                                 // roundings of a shifted image
+    double rl2_slack;           // and how much that is: 1e-9 of it (of r^2 the roundings
+                                // are 1.2e-15 L / r, and L / r < 1300)
     double box_slack;           // past a bound rounded to FP32
     // state (caller-owned)
     double *x, *y, *z, *vx, *vy, *vz;

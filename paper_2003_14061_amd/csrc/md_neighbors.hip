@@ -424,7 +424,7 @@ __device__ __forceinline__ void nl_home_cell_q(const KParams& p, const Stage& s,
                     // the image was taken before the difference: where that could
                     // decide, once more as the inclusion test rounds it
                     if (kImage == 1 &&
-                        __builtin_amdgcn_ballot_w64(fabs(r2 - p.rl2) < p.box_slack)) {
+                        __builtin_amdgcn_ballot_w64(fabs(r2 - p.rl2) < p.rl2_slack)) {
                         double ex, ey, ez;
                         lds_xyz(s.p3, (int)(enc[r] & kEntryMask), ex, ey, ez);
                         ex = xi - ex;
