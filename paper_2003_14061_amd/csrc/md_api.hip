@@ -184,8 +184,6 @@ static void plan_tiles(md_ctx* c)
     k.nl_queue = nl_queue_fits(k, k.nl_method, k.nl_block, c->lds_limit);
 }
 
-void replan_tiles(md_ctx* c) { plan_tiles(c); }
-
 static md_status hip_ok(hipError_t e) { return e == hipSuccess ? MD_OK : MD_ERR_HIP; }
 
 // Offsets of the workspace regions from their sizes.
@@ -200,22 +198,31 @@ static void relayout(md_ctx* c)
 }
 
 // Second positions (the scratch positions) for the fused steps of a cells-only
-// system without reorder, where the workspace stays within the static array's
-// size (a system that could be bound to it still can be; larger ones take the
-// separate integration pass); then lays the regions out.
+// system without reorder, where they pay (kFusedCells) and the steps can fuse: not
+// in a batch nor with bonded terms.  A system of very many cells does without where
+// they would put it past the static array (md_bind_static).  Then lays the regions
+// out.
 static void second_positions(md_ctx* c)
 {
     const md_params& p = c->prm;
-    const bool wanted =
-        p.mode == MD_CELLS_ONLY && !p.reorder && p.pipeline == MD_PIPE_TILED;
-    if (wanted) c->bytes[R_SX] = c->bytes[R_SY] = c->bytes[R_SZ] = 0;
+    if (p.mode == MD_CELLS_ONLY && !p.reorder)
+        c->bytes[R_SX] = c->bytes[R_SY] = c->bytes[R_SZ] = 0;
     relayout(c);
-    if (!wanted) return;
+    if (p.mode != MD_CELLS_ONLY || p.reorder || p.pipeline != MD_PIPE_TILED || !c->alone ||
+        c->kp.bonded_on || p.n_atoms > kFusedCells)
+        return;
     const size_t one = sizeof(double) * (size_t)p.n_atoms, more = 3 * align_up(one);
     if (c->ws_bytes + more <= MD_STATIC_WORKSPACE_BYTES) {
         c->bytes[R_SX] = c->bytes[R_SY] = c->bytes[R_SZ] = one;
         relayout(c);
     }
+}
+
+void share_machine(md_ctx* c)
+{
+    c->alone = false;
+    second_positions(c);
+    plan_tiles(c);
 }
 
 static md_status launched() { return hip_ok(hipGetLastError()); }

@@ -23,7 +23,7 @@ enum Region {
 }  // namespace md
 
 struct md_ctx;
-void replan_tiles(md_ctx* c);  // the tiling again, after a change of `alone`
+void share_machine(md_ctx* c);  // a replica of a batch: no longer alone (before md_bind)
 
 // Tuning cache (md_tune.hip): keys of a system or a batch with a candidate
 // list on this device, and the cached tuning of a key in a cache file.

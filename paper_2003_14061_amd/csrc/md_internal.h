@@ -424,9 +424,20 @@ void launch_integrate_finish(const KParams& p, int phase, int record_every, hipS
 // next kernels take flip_positions of p (a cells-only system with reorder
 // excepted: its pass reads the sorted scratch arrays and writes the state).
 // fused_fits: the tiled pipeline with scratch positions, no third law, no bonded
-// terms, and room for the partials of a recorded step (K, P per workgroup).
+// terms, and room for the partials of a recorded step (K, P per workgroup); of the
+// cells-only systems those where it pays.  There the atom's update runs in one of its
+// kCellLanes lanes, which costs more than the launches it saves from some size on.
+// Steps apart and fused: without reorder 40 000 WCA atoms 39.5 and 35.9 us, 65 000 47.9
+// and 46.6, 100 000 60.5 and 61.8, 900 000 333 and 400 (LJ 50 000 120 and 119, 65 000
+// 137 and 139); with it, which the apart passes pay for with a copy, WCA 100 000 71 and
+// 60, 900 000 420 and 375, but at 8 atoms per cell or more LJ 4000 32.4 and 29.8,
+// 16 000 51.0 and 54.2, 900 000 1290 and 1420.
+constexpr int kFusedCells = 65536, kFusedDenseCells = 8192;
 inline bool fused_fits(const KParams& p)
 {
+    if (p.mode == MD_CELLS_ONLY && p.reorder && p.n > kFusedDenseCells &&
+        p.n >= 8ll * p.ncell)
+        return false;
     return p.pipeline == MD_PIPE_TILED && p.sx && !p.newton3 && !p.bonded_on &&
            (step_part_in_ipart(p) || 6ll * p.nblk_force <= 2ll * max_force_blocks(p.n, p.ncell));
 }
