@@ -640,6 +640,32 @@ static size_t cells_lds_bytes(const KParams& p)
     return b <= 144 * 1024 ? b : 0;
 }
 
+// The largest system whose cells one workgroup builds, or the chain of kernels over
+// the whole chip beyond it.  Where most calls find nothing to do: kSortSmall.  Where
+// every call builds, the line of equal times: forced builds (md_build_cells) in one
+// workgroup and by the chain, 4000 LJ atoms 10.8 and 12.3 us, 5000 13.6 and 13.4, 7000
+// 16.8 and 13.6, 14 000 28 and 13, 6000 WCA 12.2 and 12.4; cells-only steps, 8000 LJ
+// 35.0 and 35.0, 10 007 39.8 and 37.4, 12 000 WCA 22.1 and 22.6, 16 384 42 and 25; with
+// reorder, whose permutation one CU moves, 3000 WCA 16.2 and 17.5, 4000 17.6 and 17.6,
+// 8000 27.0 and 20.3.
+static int one_workgroup_max(const KParams& p, int flags)
+{
+    if (flags & 1) return 5 * kScanThreads;
+    if (flags & kFoldBin) {
+        if (p.reorder) return 4096;
+        return p.n >= 8ll * p.ncell ? 8192 : 12288;
+    }
+    return kSortSmall;
+}
+
+// Whether k_cells_lds builds the cells of a call with these flags (with reorder it
+// leaves the copy-back to a later pass).
+static bool in_one_workgroup(const KParams& p, int flags)
+{
+    return cells_lds_bytes(p) && p.n <= one_workgroup_max(p, flags) &&
+           (!p.reorder || (flags & kFoldCopy));
+}
+
 static void cells_lds(const KParams& p, const SmallCells& a, bool bin, hipStream_t s)
 {
     const dim3 one(1), t(kScanThreads);
@@ -753,12 +779,11 @@ void launch_clear(const KParams& p, hipStream_t s) { clear_seq(Single{p}, shape_
 
 void launch_cells(const KParams& p, int flags, hipStream_t s)
 {
-    // (with reorder, k_cells_lds leaves the copy-back to a later pass)
-    if (cells_lds_bytes(p) && (!p.reorder || (flags & kFoldCopy))) {
+    if (in_one_workgroup(p, flags)) {
         cells_lds(p, SmallCells{0, 0, 0, flags & 1}, !(flags & kFoldBin), s);
         return;
     }
-    const bool small = (flags & kSortSmallOk) && p.n <= kSortSmall;
+    const bool small = (flags & kSortSmallOk) && p.n <= one_workgroup_max(p, flags);
     cells_seq(Single{p}, shape_of(p), flags, s, small ? p.n : 0);
 }
 
@@ -771,19 +796,18 @@ void launch_cell_scan(const KParams& p, hipStream_t s)
 
 bool finish_bins(const KParams& p, int flags)
 {
-    return p.mode == MD_NEIGHBOR_LIST &&
-           !(cells_lds_bytes(p) && (!p.reorder || (flags & kFoldCopy)));
+    return p.mode == MD_NEIGHBOR_LIST && !in_one_workgroup(p, flags);
 }
 
 void launch_finish_cells(const KParams& p, int flags, int phase, int record_every, bool fused,
                          hipStream_t s)
 {
-    if (cells_lds_bytes(p) && (!p.reorder || (flags & kFoldCopy))) {
+    if (in_one_workgroup(p, flags)) {
         cells_lds(p, SmallCells{fused ? 2 : 1, phase, record_every, flags & 1},
                   !(flags & kFoldBin), s);
         return;
     }
-    if ((flags & kFoldBin) && (flags & kSortSmallOk) && p.n <= kSortSmall) {
+    if ((flags & kFoldBin) && (flags & kSortSmallOk) && p.n <= one_workgroup_max(p, flags)) {
         const dim3 one(1), t(kScanThreads);
         const Single b{p};
         if (p.reorder)

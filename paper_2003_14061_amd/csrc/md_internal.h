@@ -388,7 +388,8 @@ constexpr int kBinDone = 16;  // k_bin_finish has binned the atoms
 // cells in one workgroup (k_cells_lds).  The line: an atom fits 14 bits beside
 // its cell, and past it the tables no longer fit 144 KiB; one CU's memory path
 // makes the rebuild itself slower than the whole chip's from about 5000 atoms
-// on, but idle steps (11 of 12) cost 2 us against 8.
+// on, but idle steps (11 of 12) cost 2 us against 8.  Calls that always build have
+// lower lines (one_workgroup_max).
 constexpr int kSortSmall = 16384;
 void launch_cells(const KParams& p, int flags, hipStream_t s);
 void launch_neighbors(const KParams& p, int force, hipStream_t s);
