@@ -869,16 +869,17 @@ static void fused_bodies(const md_ctx* c, hipStream_t s, int32_t n, int32_t reco
     }
 }
 
-// n_graphs replays of the graph of len steps, captured first if needed.
-// The null stream cannot be captured: then the graph runs on the context's own
-// stream, ordered after and before the bound stream's work by events.
-// fused: the steps are fused bodies (fused_bodies), the first from flip.
-static md_status step_graphs(md_ctx* c, int32_t len, int32_t n_graphs, int32_t record_every,
-                             bool fused, bool& flip)
+// The graph of len steps, captured unless it is there already.  The null stream
+// cannot be captured: then the graph runs on the context's own stream, ordered after
+// and before the bound stream's work by events.
+// fused: the steps are fused bodies (fused_bodies), the first from flip.  Called
+// before the first launch of md_step, so that a call that cannot have its graph (its
+// stream is being captured, say) leaves the state as it was.
+static md_status step_graph_ready(md_ctx* c, int32_t len, int32_t record_every, bool fused,
+                                  bool flip)
 {
     hipStream_t run = c->stream;
-    const bool own = run == nullptr;
-    if (own) {
+    if (run == nullptr) {
         if (!c->gstream &&
             hipStreamCreateWithFlags(&c->gstream, hipStreamNonBlocking) != hipSuccess)
             return MD_ERR_HIP;
@@ -889,39 +890,44 @@ static md_status step_graphs(md_ctx* c, int32_t len, int32_t n_graphs, int32_t r
         run = c->gstream;
     }
     const int kind = fused ? (flip ? 2 : 1) : 0;
-    if (!(c->gexec && c->g_record == record_every && c->g_run == run && c->g_len == len &&
-          c->g_kind == kind)) {
+    if (c->gexec && c->g_record == record_every && c->g_run == run && c->g_len == len &&
+        c->g_kind == kind)
+        return MD_OK;
+    drop_graph(c);
+    if (hipStreamBeginCapture(run, hipStreamCaptureModeThreadLocal) != hipSuccess)
+        return MD_ERR_HIP;
+    md_status st = MD_OK;
+    bool f = flip;
+    if (fused)
+        fused_bodies(c, run, len, record_every, f);
+    else
+        st = step_launches(c, run, false, len, record_every, 0);
+    hipGraph_t g = nullptr;
+    const hipError_t ec = hipStreamEndCapture(run, &g);
+    if (st != MD_OK) return st;
+    if (ec != hipSuccess || !g) return MD_ERR_HIP;
+    c->graph = g;
+    if (hipGraphInstantiate(&c->gexec, c->graph, nullptr, nullptr, 0) != hipSuccess) {
         drop_graph(c);
-        if (hipStreamBeginCapture(run, hipStreamCaptureModeThreadLocal) != hipSuccess)
-            return MD_ERR_HIP;
-        md_status st = MD_OK;
-        bool f = flip;
-        if (fused)
-            fused_bodies(c, run, len, record_every, f);
-        else
-            st = step_launches(c, run, false, len, record_every, 0);
-        hipGraph_t g = nullptr;
-        const hipError_t ec = hipStreamEndCapture(run, &g);
-        if (st != MD_OK) return st;
-        if (ec != hipSuccess || !g) return MD_ERR_HIP;
-        c->graph = g;
-        if (hipGraphInstantiate(&c->gexec, c->graph, nullptr, nullptr, 0) != hipSuccess) {
-            drop_graph(c);
-            return MD_ERR_HIP;
-        }
-        c->g_record = record_every;
-        c->g_kind = kind;
-        c->g_len = len;
-        c->g_run = run;
+        return MD_ERR_HIP;
     }
+    c->g_record = record_every;
+    c->g_kind = kind;
+    c->g_len = len;
+    c->g_run = run;
+    return MD_OK;
+}
+
+// n_graphs replays of the graph of step_graph_ready.
+static md_status step_graphs(md_ctx* c, int32_t n_graphs)
+{
+    hipStream_t run = c->g_run;
+    const bool own = run != c->stream;
     if (own && (hipEventRecord(c->gev[0], c->stream) != hipSuccess ||
                 hipStreamWaitEvent(run, c->gev[0], 0) != hipSuccess))
         return MD_ERR_HIP;
     for (int32_t g = 0; g < n_graphs; ++g)
         if (hipGraphLaunch(c->gexec, run) != hipSuccess) return MD_ERR_HIP;
-    // several replays are of kGraphSteps (even) bodies each: the places are the
-    // same before and after
-    if (fused && len % 2 != 0 && fused_flips(c->kp)) flip = !flip;
     if (own && (hipEventRecord(c->gev[1], run) != hipSuccess ||
                 hipStreamWaitEvent(c->stream, c->gev[1], 0) != hipSuccess))
         return MD_ERR_HIP;
@@ -934,43 +940,49 @@ extern "C" md_status md_step(md_ctx* c, int32_t n_steps, int32_t record_every)
     if (!c->bound) return MD_ERR_NOT_BOUND;
     if (!c->forces_ok) return MD_ERR_STATE;
     if (n_steps == 0) return MD_OK;
-    md_status st;
+    md_status st = MD_OK;
     const int64_t step0 = c->host_steps;
-    bool flip = false;
-    if (fused_steps(c)) {
+    const bool fused = fused_steps(c);
+    // the steps behind the first, and the graphs they replay
+    const int32_t rest = n_steps - 1;
+    const bool graph =
+        c->graph_on && n_steps > kGraphMin && (fused || !(c->timing || layer_reorder_on(c)));
+    const int32_t len = rest < kGraphSteps ? rest : kGraphSteps, n_graphs = graph ? rest / len : 0;
+    bool flip = fused && fused_flips(c->kp) && rest % 2 != 0;
+    if (graph && (st = step_graph_ready(c, len, record_every, fused, flip)) != MD_OK) {
+        (void)hipGetLastError();  // reported here, not by the next call's launches
+        return st;
+    }
+    if (fused) {
         const KParams& k = c->kp;
         hipStream_t s = c->stream;
-        const int32_t rest = n_steps - 1;
         const bool nl = k.mode == MD_NEIGHBOR_LIST;
         const int flags = fused_cells_flags(k);
-        flip = fused_flips(k) && rest % 2 != 0;
         launch_integrate_pass(k, 0, s, !nl, flip);
         launch_finish_cells(flipped(k, flip), flags, 0, record_every, false, s);
-        st = MD_OK;
-        if (!c->graph_on || n_steps <= kGraphMin) {
-            fused_bodies(c, s, rest, record_every, flip);
-        } else {
-            const int32_t len = rest < kGraphSteps ? rest : kGraphSteps, n_graphs = rest / len;
-            st = step_graphs(c, len, n_graphs, record_every, true, flip);
-            if (st == MD_OK) fused_bodies(c, s, rest - n_graphs * len, record_every, flip);
-        }
+        if (graph) st = step_graphs(c, n_graphs);
+        // several replays are of kGraphSteps (even) bodies each: the places are the
+        // same before and after
+        if (graph && len % 2 != 0 && fused_flips(k)) flip = !flip;
         if (st == MD_OK) {
+            fused_bodies(c, s, rest - n_graphs * len, record_every, flip);
             if (nl) launch_neighbors(k, kFoldCopy, s);
             launch_forces(k, s, nl ? 0 : flags & kFoldCopy);
         }
-    } else if (c->timing || !c->graph_on || layer_reorder_on(c) || n_steps <= kGraphMin) {
+    } else if (!graph) {
         st = step_launches(c, c->stream, true, n_steps, record_every, step0);
     } else {
-        const int32_t rest = n_steps - 1;
-        const int32_t len = rest < kGraphSteps ? rest : kGraphSteps, n_graphs = rest / len;
         st = step_launches(c, c->stream, true, 1, record_every, step0);
-        if (st == MD_OK) st = step_graphs(c, len, n_graphs, record_every, false, flip);
+        if (st == MD_OK) st = step_graphs(c, n_graphs);
         if (st == MD_OK)
             st = step_launches(c, c->stream, false, rest - n_graphs * len, record_every,
                                step0 + 1 + (int64_t)n_graphs * len);
     }
     c->host_steps = step0 + n_steps;
-    if (st != MD_OK) return st;
+    if (st != MD_OK) {
+        c->forces_ok = false;  // stopped between steps (a replay failed)
+        return st;
+    }
     launch_integrate(c->kp, 2, record_every, c->stream);
     return launched();
 }
