@@ -335,12 +335,13 @@ typedef struct {
     int32_t force_block;    /* threads per workgroup of the force pass: 64..1024, multiple of 64
                                (512 after md_init) */
     int32_t nl_block;       /* threads per workgroup of the list build: 64..1024, multiple of 64;
-                               0 = automatic (a lane per home atom of a mean tile, or a wave
-                               per home cell of the widest tile, at most 16 waves) */
+                               0 = automatic (a lane per home atom of a mean tile, or 4 to 16
+                               waves that share the home cells of the widest tile) */
     int32_t tile_cells;     /* neighbor-list mode: cells per tile (a block of cells) along x;
-                               0 = automatic: the block with the fewest staged cells per home
-                               cell whose staged atoms fit three force workgroups per CU and
-                               whose home atoms fill at most three force passes */
+                               0 = automatic: the block of the least estimated cost of a force
+                               pass (rounds of workgroups over the CUs) whose staged atoms fit
+                               three force workgroups per CU and whose home atoms fill at most
+                               three passes of one */
     int32_t stage_cap;      /* atoms a workgroup stages in LDS (0 = 1.15x the mean need plus
                                64); tiles that hold more read positions from global memory
                                instead */
@@ -358,7 +359,11 @@ typedef struct {
 /* md_set_tuning: change the launch shape (host only; takes effect at the
  * next launch).  The forces must be recomputed (md_forces) before md_step,
  * and a change of the tile size also needs md_build_neighbors, since list
- * entries index the tile's staged atoms.  md_get_tuning: the current shape
+ * entries index the tile's staged atoms.  An automatic tile size depends on
+ * force_lanes and force_block too; while a list stands and the requested tile
+ * size stays as it was, the size in use is kept, and chosen again by the next
+ * md_build_cells or md_build_neighbors if no md_forces has used it by then.
+ * md_get_tuning: the current shape
  * (tile_cells, tile_y, tile_z as resolved: the largest block in use). */
 md_status md_set_tuning(md_ctx* ctx, const md_tuning* tuning);
 md_status md_get_tuning(const md_ctx* ctx, md_tuning* tuning);

@@ -77,10 +77,8 @@ static double tiling_cost(const KParams& k, int64_t tiles, double home, double s
 // tiles), 29.4 at 2 x 2 x 2 (216); 70 000 LJ 37.0 and 33.6 (320 and 512 tiles);
 // 700 000 WCA 76.7 and 65.6 (1156 and 1445); over 27 sizes of both from 500 to 2.048M
 // atoms it picks a shape within 0.9% of the best one measured, on average, and
-// never a slower one than before by more than the runs differ.  The LDS
-// capacity then allows 1.15x the mean staged count plus 64 of the largest
-// block; a tile that does not fit takes its partners from global memory.
-static void plan_tiles(md_ctx* c)
+// never a slower one than before by more than the runs differ.
+static void plan_shape(md_ctx* c)
 {
     KParams& k = c->kp;
     const int nc = k.nc;
@@ -130,6 +128,17 @@ static void plan_tiles(md_ctx* c)
     c->tile_cells_res = k.kx_max;
     c->tile_y_res = k.ky_max;
     c->tile_z_res = k.kz_max;
+}
+
+// The tiles' shape (keep: the one there is) and what follows from it.  The LDS
+// capacity allows 1.15x the mean staged count plus 64 of the largest block; a tile
+// that does not fit takes its partners from global memory.
+static void plan_tiles(md_ctx* c, bool keep = false)
+{
+    if (!keep) plan_shape(c);
+    c->replan = keep;
+    KParams& k = c->kp;
+    const double occ = (double)k.n / ((double)k.nc * k.nc * k.nc);
     const double s_mean = (double)(k.kx_max + 2) * (k.ky_max + 2) * (k.kz_max + 2) * occ;
     // tables and static LDS
     const size_t tables = stage_bytes(k, 0) + 2048;
@@ -632,6 +641,7 @@ extern "C" md_status md_build_cells(md_ctx* c)
 {
     if (!c) return MD_ERR_ARG;
     if (!c->bound) return MD_ERR_NOT_BOUND;
+    if (c->replan) plan_tiles(c);
     cells_any(c->kp, 1, c->stream);
     c->cells_ok = true;
     c->nl_ok = false;
@@ -645,6 +655,7 @@ extern "C" md_status md_build_neighbors(md_ctx* c)
     if (!c->bound) return MD_ERR_NOT_BOUND;
     if (c->prm.mode != MD_NEIGHBOR_LIST) return MD_ERR_ARG;
     if (!c->cells_ok) return MD_ERR_STATE;
+    if (c->replan) plan_tiles(c);
     neighbors_any(c->kp, 1, c->stream);
     c->nl_ok = true;
     return launched();
@@ -722,6 +733,7 @@ extern "C" md_status md_forces(md_ctx* c)
     if (!c) return MD_ERR_ARG;
     if (!c->bound) return MD_ERR_NOT_BOUND;
     if (!c->cells_ok || (c->prm.mode == MD_NEIGHBOR_LIST && !c->nl_ok)) return MD_ERR_STATE;
+    c->replan = false;  // the list in use has the shape that was kept
     timed_forces(c);
     c->forces_ok = true;
     return launched();
@@ -1134,6 +1146,7 @@ static void checkpoint_arrays(void* ws, const TrajLayout& L, int seg, double** o
 // Cells, list and forces from scratch at the current positions.
 static void rebuild_all(md_ctx* c)
 {
+    c->replan = false;
     launch_cells(c->kp, 1, c->stream);
     launch_neighbors(c->kp, 1, c->stream);
     launch_forces(c->kp, c->stream);
@@ -1152,7 +1165,10 @@ extern "C" md_status md_traj_forward(md_ctx* c, const md_traj_params* tp, void* 
     md_status st = traj_check(c, tp, ws, &L);
     if (st != MD_OK) return st;
     if (!obs) return MD_ERR_ARG;
-    if (!c->forces_ok) rebuild_all(c);
+    if (!c->forces_ok) {
+        if (c->replan) plan_tiles(c);
+        rebuild_all(c);
+    }
     double* ck[6];
     // the segments launch directly: on a system made for one trajectory (the
     // usual case, since eps and sigma are fixed at md_init) capturing a graph
@@ -1344,6 +1360,11 @@ extern "C" md_status md_set_tuning(md_ctx* c, const md_tuning* t)
     KParams& k = c->kp;
     drop_graph(c);  // launch shapes and parameters are baked into it
     const int old[4] = {k.n_tiles, k.kx_max, k.ky_max, k.kz_max};
+    // the automatic shape also follows from the force pass's lanes and workgroup: under a
+    // list that stands it is chosen again by the next list build, so that a change of
+    // those alone leaves the list as it is
+    const bool keep = c->nl_ok && t->tile_cells == c->tile_cells && t->tile_y == c->tile_y &&
+                      t->tile_z == c->tile_z;
     k.force_lanes = t->force_lanes;
     k.force_block = t->force_block;
     c->nl_block_req = t->nl_block;
@@ -1353,7 +1374,7 @@ extern "C" md_status md_set_tuning(md_ctx* c, const md_tuning* t)
     c->tile_cells = t->tile_cells;
     c->tile_y = t->tile_y;
     c->tile_z = t->tile_z;
-    plan_tiles(c);
+    plan_tiles(c, keep);
     // the list encoding depends on the tiling
     if (k.n_tiles != old[0] || k.kx_max != old[1] || k.ky_max != old[2] || k.kz_max != old[3])
         c->nl_ok = false;

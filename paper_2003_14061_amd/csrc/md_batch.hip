@@ -355,8 +355,13 @@ extern "C" md_status md_batch_set_tuning(md_batch* b, const md_tuning* t)
     if (!b || !t) return MD_ERR_ARG;
     const int R = (int)b->rep.size();
     for (md_ctx* c : b->rep) {
+        const bool nl_ok = c->nl_ok;
+        c->nl_ok = false;  // the lists are built anew in any case: no shape is kept
         md_status st = md_set_tuning(c, t);
-        if (st != MD_OK) return st;
+        if (st != MD_OK) {
+            c->nl_ok = nl_ok;
+            return st;
+        }
         if (t->integrate_grid == 0) c->kp.int_grid = integrate_share(c->prm.n_atoms);
     }
     b->prepared = false;

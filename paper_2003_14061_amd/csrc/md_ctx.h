@@ -56,6 +56,7 @@ struct md_ctx {
     int tile_cells = 0, tile_y = 0, tile_z = 0;  // requested block size (0: automatic)
     int tile_cells_res = 0, tile_y_res = 0, tile_z_res = 0;  // largest block in use
     int stage_cap = 0;              // requested staged-atom capacity (0: from density)
+    bool replan = false;            // the next md_build_* chooses the tiles' shape again
     bool alone = true;              // the system has the machine to itself (plan_tiles)
     // md_step's graph of kGraphSteps steps (see md_api.hip)
     bool graph_on = false;  // set by md_init from the system size
