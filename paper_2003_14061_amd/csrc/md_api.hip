@@ -89,15 +89,18 @@ static void plan_shape(md_ctx* c)
         const int parts = (nc + req - 1) / req;
         return (nc + parts - 1) / parts;
     };
+    const auto request = [nc](int req) { return req < nc ? req : nc; };
+    const int req_x = request(c->tile_cells), req_y = request(c->tile_y),
+              req_z = request(c->tile_z);
     int best[3] = {1, 1, 1};
     double best_score = 1e300;
     const int kx_hi = nc < 64 ? nc : 64, kyz_hi = nc < 4 ? nc : 4;
     for (int kz = 1; kz <= kyz_hi; ++kz)
         for (int ky = kz; ky <= kyz_hi; ++ky)
             for (int kx = ky; kx <= kx_hi; ++kx) {
-                const int ax = c->tile_cells > 0 ? c->tile_cells : kx;
-                const int ay = c->tile_y > 0 ? c->tile_y : ky;
-                const int az = c->tile_z > 0 ? c->tile_z : kz;
+                const int ax = req_x > 0 ? req_x : kx;
+                const int ay = req_y > 0 ? req_y : ky;
+                const int az = req_z > 0 ? req_z : kz;
                 const int mx = maxsize(ax), my = maxsize(ay), mz = maxsize(az);
                 const double cells = (double)(mx + 2) * (my + 2) * (mz + 2);
                 const double staged = cells * occ;
