@@ -353,7 +353,8 @@ typedef struct {
                                is the same either way.  md_get_tuning reports the method
                                in use */
     int32_t tile_y;         /* cells per tile along y (0 = automatic, as tile_cells) */
-    int32_t tile_z;         /* cells per tile along z (0 = automatic, as tile_cells) */
+    int32_t tile_z;         /* cells per tile along z (0 = automatic, as tile_cells); y times z
+                               at most 64: a larger request is reduced, z first */
 } md_tuning;
 
 /* md_set_tuning: change the launch shape (host only; takes effect at the

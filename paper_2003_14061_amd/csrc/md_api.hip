@@ -89,9 +89,12 @@ static void plan_shape(md_ctx* c)
         const int parts = (nc + req - 1) / req;
         return (nc + parts - 1) / parts;
     };
-    const auto request = [nc](int req) { return req < nc ? req : nc; };
-    const int req_x = request(c->tile_cells), req_y = request(c->tile_y),
-              req_z = request(c->tile_z);
+    const auto request = [](int req, int most) { return req < most ? req : most; };
+    const int rows = nc < kHomeRows ? nc : kHomeRows;
+    const int req_x = request(c->tile_cells, nc), req_y = request(c->tile_y, rows);
+    const int req_z = request(c->tile_z, req_y > 0 && rows > kHomeRows / maxsize(req_y)
+                                             ? kHomeRows / maxsize(req_y)
+                                             : rows);
     int best[3] = {1, 1, 1};
     double best_score = 1e300;
     const int kx_hi = nc < 64 ? nc : 64, kyz_hi = nc < 4 ? nc : 4;
@@ -102,6 +105,7 @@ static void plan_shape(md_ctx* c)
                 const int ay = req_y > 0 ? req_y : ky;
                 const int az = req_z > 0 ? req_z : kz;
                 const int mx = maxsize(ax), my = maxsize(ay), mz = maxsize(az);
+                if (my * mz > kHomeRows) continue;  // (one row of the other axis never is)
                 const double cells = (double)(mx + 2) * (my + 2) * (mz + 2);
                 const double staged = cells * occ;
                 const double home = (double)mx * my * mz * occ;

@@ -132,6 +132,9 @@ __device__ __forceinline__ void lds_xyz(const MD_LDS double* a, int e, double& x
     z = q[2];
 }
 
+// Most home rows of a tile: a wave numbers them, a row per lane (stage_tables).
+constexpr int kHomeRows = kWave;
+
 // Staged cells of the largest tile.
 __host__ __device__ __forceinline__ int stage_cells_max(const KParams& p)
 {
@@ -238,7 +241,7 @@ __device__ __forceinline__ void stage_tables(const KParams& p, const Tile& g, St
     s.fits = s.total < s.cap;
     __syncthreads();
     // home rows r = (c - 1) ky + (b - 1): the prefix of their home atoms (one wave,
-    // a row per lane, at most 64 rows)
+    // a row per lane, at most kHomeRows)
     if (threadIdx.x < kWave) {
         const int r = threadIdx.x;
         int cnt = 0;
