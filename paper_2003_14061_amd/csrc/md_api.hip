@@ -366,9 +366,8 @@ extern "C" md_status md_init(const md_params* in, md_ctx** out)
     k.inv_w = (double)nc / p.L;
     k.rc2 = p.r_cut * p.r_cut;
     k.rl2 = r_list * r_list;
-    k.rl2_slack = 1e-9 * k.rl2;
-    k.rl2_in = k.rl2 - k.rl2_slack;
-    k.box_reach2 = k.rl2 + k.rl2_slack;
+    k.rl2_in = k.rl2 * (1.0 - 1e-9);
+    k.box_reach2 = k.rl2 * (1.0 + 1e-9);
     k.box_slack = 1e-6 * p.L;
     k.sig2 = p.sigma * p.sigma;
     k.eps2 = 2.0 * p.eps;

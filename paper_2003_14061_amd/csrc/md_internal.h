@@ -53,8 +53,7 @@ struct KParams {
     double ushift2;         // 2 ushift = shift / (2 eps): the constant of the lean sums
     double eps, sigma;
     double rl2_in, box_reach2;  // the list radius squared, less and more than the
-                                // roundings of a shifted image
-    double rl2_slack;           // and how much that is: 1e-9 of it (of r^2 the roundings
+                                // roundings of a shifted image: 1e-9 of it (of r^2 they
                                 // are 1.2e-15 L / r, and L / r < 1300)
     double box_slack;           // past a bound rounded to FP32
     // state (caller-owned)

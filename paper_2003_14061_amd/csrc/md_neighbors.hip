@@ -420,11 +420,10 @@ __device__ __forceinline__ void nl_home_cell_q(const KParams& p, const Stage& s,
                 auto test = [&](int r) {
                     const double dx = xi - cx[r], dy = yi - cy[r], dz = zi - cz[r];
                     const double r2 = dist2(dx, dy, dz);
-                    mk[r] = __builtin_amdgcn_ballot_w64(r2 < p.rl2);
+                    mk[r] = __builtin_amdgcn_ballot_w64(r2 < (kImage == 1 ? p.rl2_in : p.rl2));
                     // the image was taken before the difference: where that could
                     // decide, once more as the inclusion test rounds it
-                    if (kImage == 1 &&
-                        __builtin_amdgcn_ballot_w64(fabs(r2 - p.rl2) < p.rl2_slack)) {
+                    if (kImage == 1 && __builtin_amdgcn_ballot_w64(r2 < reach2) != mk[r]) {
                         double ex, ey, ez;
                         lds_xyz(s.p3, (int)(enc[r] & kEntryMask), ex, ey, ez);
                         ex = xi - ex;
