@@ -227,6 +227,8 @@ def run_gpu(w, precision, steps, warmup, newton3=False, pipeline="tiled", detail
                        "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                        "traffic": measured_traffic(w.n, precision),
                        "kernel": "k_forces_tiles", "bytes_per_atom": round(bpa, 2),
+                       "launches": "event-timed steps with the integration apart; the timed "
+                                   "steps run it fused with the integration (k_forces_step)",
                        "units_per_launch": w.n,
                        "alu": {"achieved": round(flops, 2), "peak": alu_peak, "unit": "TFLOP/s",
                                "frac": round(flops / alu_peak, 4),
@@ -405,7 +407,7 @@ def run_polymer(steps=500, warmup=50):
             **out,
             "bonded_overhead_ms_per_step": round(out["bonded"]["ms_per_step"]
                                                  - out["pairs_only"]["ms_per_step"], 6),
-            "kernels": "k_bond_map (gated with the cell rebuild) + k_bonded (thread per atom)"}
+            "kernels": "k_bonded (thread per atom); the map of slots is written by the cell sort"}
 
 
 def run_adjoint(precision, repeats=3):

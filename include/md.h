@@ -308,8 +308,10 @@ md_status md_step(md_ctx* ctx, int32_t n_steps, int32_t record_every);
  * launched directly.  A call of 10 to 32 steps replays one graph of all its
  * steps but the first (recaptured when that length changes), and calls of up
  * to 9 steps launch directly.  The default is off: direct launches measured
- * 9-20% faster per step on MI355X for 4000 to 131 072 atoms, so the graph is
- * for callers that want the steps as a graph.  When the bound stream is the
+ * 2-18% faster per step on MI355X for 500 to 256 000 atoms, so the graph is
+ * for callers that want the steps as a graph.  A call whose graph cannot be
+ * captured (its stream is being captured already) returns MD_ERR_HIP and
+ * leaves the state as it was.  When the bound stream is the
  * null stream the graph runs on a stream of the context's own, ordered after
  * the bound stream's earlier work and before its later work by events.
  * enable = 0 launches every kernel directly.  Results are identical either

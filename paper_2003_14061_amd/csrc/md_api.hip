@@ -176,7 +176,7 @@ static void plan_tiles(md_ctx* c, bool keep = false)
         waves = waves > 16 ? 16 : waves;
     } else {
         // few tiles, which leave room on the CUs: a wave per home cell of a tile of
-        // 12 (100 003 LJ atoms, 486 tiles: 60 against 76 us; 2.048M, 8640 tiles:
+        // 12 (100 003 LJ atoms, 486 tiles: 60 against 76 us; 2.048M, 9216 tiles:
         // 723 against 668 us, as two such workgroups share a CU instead of three)
         waves = home_cells >= 12 && c->alone && k.n_tiles < 3 * 256
                     ? 12
@@ -747,20 +747,18 @@ extern "C" md_status md_forces(md_ctx* c)
 
 // ---- md_step ----
 //
-// A step is a fixed launch sequence (integrate, the rebuild-gated cell and
-// list kernels, forces), so runs of kGraphSteps steps can be captured once
-// into a HIP graph and replayed (md_set_graph), for callers that need the
-// step as a graph.  It is off by default: with the present launch sequence
-// (an integration pass and its one-workgroup finish, the gated cell and list
-// kernels, the force pass) direct launches measured faster on MI355X at
-// every size tried, 9-20% per step for 4000 to 131 072 atoms (4000-atom WCA
-// cells-only 29.7 against 32.4 us, 32 000-atom LJ 38.2 against 45.9 us).
-// The first step of a call (its integrate kernel
-// only kicks and drifts) and the remainder are launched directly.  A call of
-// fewer than kGraphSteps + 1 steps (but at least kGraphMin + 1) replays one
-// graph of its own length instead, so that repeated short calls (the
-// adjoint's forward segments) are captured too; the graph is recaptured when
-// the length changes.  Timing (md_set_timing) brackets each force launch with
+// A step is a fixed launch sequence (the rebuild-gated list build, the fused force
+// pass, the finish with the rebuild-gated cell build), so runs of kGraphSteps steps can
+// be captured once into a HIP graph and replayed (md_set_graph), for callers that
+// need the step as a graph.  It is off by default: direct launches measured faster on
+// MI355X or the same (per step, direct and replayed: 4000-atom WCA cells-only 12.6 and
+// 13.9 us; lists: 10 007 LJ 20.9 and 23.5, 32 000 WCA 24.6 and 25.1, 32 000 LJ 28.4 and
+// 33.5, 131 072 WCA 26.6 and 32.4, 256 000 WCA 31.9 and 37.9).
+// The first step of a call (its integrate kernel only kicks and drifts) and the
+// remainder are launched directly.  A call of fewer than kGraphSteps + 1 steps (but
+// at least kGraphMin + 1) replays one graph of its own length instead, so that
+// repeated short calls are captured too; the graph is recaptured when the length
+// changes.  Timing (md_set_timing) brackets each force launch with
 // events and uses the direct path throughout.
 
 constexpr int kGraphSteps = 32;

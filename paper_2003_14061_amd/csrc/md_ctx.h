@@ -59,7 +59,7 @@ struct md_ctx {
     bool replan = false;            // the next md_build_* chooses the tiles' shape again
     bool alone = true;              // the system has the machine to itself (plan_tiles)
     // md_step's graph of kGraphSteps steps (see md_api.hip)
-    bool graph_on = false;  // set by md_init from the system size
+    bool graph_on = false;  // set by md_set_graph
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
     int g_record = -1;                     // record_every the graph was captured with

@@ -1,7 +1,7 @@
 // md_finish.h -- the per-system finish of an integration pass (reductions of
 // section 2.3 F2, step count and history, rebuild decision), shared by the
-// finish kernel and the small-system cell sort that takes it over in
-// cells-only steps.
+// finish kernel and the kernels that take it over: the binning of list steps
+// (k_bin_finish) and the one-workgroup cell builds.
 #pragma once
 #include "md_device.h"
 

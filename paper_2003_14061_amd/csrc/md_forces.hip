@@ -22,7 +22,7 @@
 // fit in LDS add straight into the force arrays.  The order of the atomic
 // adds is not fixed, so the forces are reproducible to rounding only.
 //
-// Cells-only mode: one lane per atom walks the 27 surrounding cells.
+// Cells-only mode: kCellLanes lanes per atom, a surrounding cell each.
 //
 // Precision: FP64 forms everything in double.  FP32-mixed forms the pair
 // separation and the cutoff test in double, then the pair force, energy and

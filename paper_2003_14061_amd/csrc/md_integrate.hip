@@ -11,9 +11,9 @@
 // paper refreshes "at intervals of several time steps", section 2.3, from a
 // bound on the maximal velocity; here the bound is the displacement itself).
 //
-// Between the steps of one call the tiled list pipeline with reorder does
-// this pass inside the force pass instead (k_forces_step), with the same
-// operations per atom.
+// Between the steps of one call the tiled pipeline does this pass inside the
+// force pass where it can (fused_fits: k_forces_step, k_cells_step; a trajectory's
+// segments too), with the same operations per atom.
 //
 // Reductions (section 2.3, F2): each integration workgroup writes its
 // partial sums, and k_int_finish, one workgroup per system launched right
