@@ -290,14 +290,19 @@ __device__ __forceinline__ uint32_t wave_umax(uint32_t v)
 }
 
 // Middle and half width, rounded outward past the FP32 conversion, of the
-// interval the lanes' v span (v > -L).
+// interval the lanes' v span.  The order of the bits and the slack hold for v of
+// [-L, 3 L); an atom that left the box by more, which folding by one box length
+// leaves in a cell at its edge, or a NaN, makes the half width infinite (the middle
+// then still lies on the cell's side of the box, as near_image needs).
 __device__ __forceinline__ void wave_span(const KParams& p, double v, double& mid, double& half)
 {
-    const uint32_t b = __builtin_bit_cast(uint32_t, (float)(v + p.L));
-    const double hi = (double)__builtin_bit_cast(float, wave_umax(b)) - p.L;
-    const double lo = (double)__builtin_bit_cast(float, ~wave_umax(~b)) - p.L;
-    mid = 0.5 * (lo + hi);
-    half = 0.5 * (hi - lo) + p.box_slack;
+    const uint32_t b = __builtin_bit_cast(uint32_t, (float)__builtin_fma(v, p.invL, 1.0));
+    const uint32_t bh = wave_umax(b);
+    const double hi = (double)__builtin_bit_cast(float, bh);
+    const double lo = (double)__builtin_bit_cast(float, ~wave_umax(~b));
+    mid = __builtin_fma(0.5 * (lo + hi), p.L, -p.L);
+    half = __builtin_fma(0.5 * (hi - lo), p.L, p.box_slack);
+    if (bh >= 0x40800000u) half = __builtin_inf();  // 4.0f, or a negative number
 }
 
 // The image of candidate (cx, cy, cz) on the side of (bx, by, bz) in each
@@ -341,20 +346,22 @@ __device__ __forceinline__ void nl_home_cell_q(const KParams& p, const Stage& s,
         const bool home_lane = lane < nhs;
         const int hl = h0 + (home_lane ? lane : 0);
         const int slot_l = atom_at(p, hslot0 + (hl - hb));
-        double bx, by, bz, wx, wy, wz;  // the home atoms' box: middle, half widths
-        {
-            double hx, hy, hz;
-            lds_xyz(s.p3, hl, hx, hy, hz);
-            wave_span(p, hx, bx, wx);
-            wave_span(p, hy, by, wy);
-            wave_span(p, hz, bz, wz);
-        }
         int mreg = 0;        // lane hh: home atom hh's list length so far
         uint64_t part = 0;   // lane hh: its last, incomplete chunk
         int qn = 0;          // candidates queued
         int sg = 0, e0 = 0, ee = 0, t0 = 0;  // window being gathered: entries e0 .. ee - 1 left
         bool more = true;
         while (more) {
+            // the home atoms' box: middle, half widths (anew for each block of candidates, of
+            // which most cells have one: kept across the tests it would be spilled)
+            double bx, by, bz, wx, wy, wz;
+            {
+                double hx, hy, hz;
+                lds_xyz(s.p3, hl, hx, hy, hz);
+                wave_span(p, hx, bx, wx);
+                wave_span(p, hy, by, wy);
+                wave_span(p, hz, bz, wz);
+            }
             // gather until the queue is full or the windows end
             while (qn < kQueue) {
                 if (e0 >= ee) {
